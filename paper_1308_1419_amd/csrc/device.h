@@ -42,6 +42,26 @@ __device__ __forceinline__ void g_lambda(uint32_t lam, uint32_t &i, uint32_t &j)
   j = (uint32_t)(lam - t);
 }
 
+// g_lambda for a lambda that is the same in every lane: the guess moves to a
+// scalar register and the fix-up runs on the scalar unit.  The column under
+// the guessed row lies between -r and 2 r + 1, so 32-bit differences do (the
+// scalar unit has no 64-bit ordered compare).
+__device__ __forceinline__ void g_lambda_uniform(uint32_t lam, uint32_t &i, uint32_t &j) {
+  const float x = __builtin_fmaf(2.0f, (float)lam, 0.25f);
+  const float s = x * __builtin_amdgcn_rsqf(x);
+  int32_t r = (int32_t)__builtin_amdgcn_readfirstlane((uint32_t)__builtin_fmaxf(s - 0.5f, 0.0f));
+  int32_t c = (int32_t)(lam - (uint32_t)tri64((uint32_t)r));
+  if (c < 0) {
+    c += r;  // T(r - 1) = T(r) - r
+    --r;
+  } else if (c > r) {
+    c -= r + 1;  // T(r + 1) = T(r) + r + 1
+    ++r;
+  }
+  i = (uint32_t)r;
+  j = (uint32_t)c;
+}
+
 // The map without the diagonal (Sec. II-A, Eq. (10)): lambda enumerates the
 // cells j < i row by row, row i starting at S(i) = i(i-1)/2, and
 // i = floor(sqrt(1/4 + 2 lambda) + 1/2), j = lambda - S(i) (the column is

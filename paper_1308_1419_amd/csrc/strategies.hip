@@ -8,6 +8,8 @@
 // counts blocks / fully idle blocks / idle threads instead of storing, the
 // other is the paper's dummy kernel (Sec. III-A, Sec. IV), which measures
 // the cost of the map alone.
+#include <type_traits>
+
 #include "device.h"
 #include "kernels.h"
 
@@ -170,6 +172,168 @@ __global__ void rec_cell_kernel(EdmArgs a, int mode, uint32_t side, uint32_t nb,
 }
 
 // ---------------------------------------------------------------------------
+// more than four features: the same blocks, points staged per block
+// ---------------------------------------------------------------------------
+
+// Lane K of each 16-lane row, in every lane of the row (row_newbcast folds
+// into the subtraction that consumes it).
+template <int K>
+__device__ __forceinline__ float row_lane(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), 0x150 + K,
+                                                               0xF, 0xF, true));
+}
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+// Four features of the pair sum, in feature order (the operation order of
+// pair_dist).
+template <int K>
+__device__ __forceinline__ float add_features(float s, float row, f4 c) {
+  const float c0 = c[0], c1 = c[1], c2 = c[2], c3 = c[3];
+  float t = row_lane<K>(row) - c0;
+  s = __builtin_fmaf(t, t, s);
+  t = row_lane<K + 1>(row) - c1;
+  s = __builtin_fmaf(t, t, s);
+  t = row_lane<K + 2>(row) - c2;
+  s = __builtin_fmaf(t, t, s);
+  t = row_lane<K + 3>(row) - c3;
+  return __builtin_fmaf(t, t, s);
+}
+
+// LTM, BB and REC blocks (rho x rho threads on a rho x rho square of cells,
+// one cell per thread) for d > 4.  A thread that reads its two points on its
+// own issues 2 d loads, and a wave's 64 column loads touch 16 to 32 rows of
+// X each: at N = 8000, d = 16, rho = 16 (full layout, LTM) the launch took
+// 907 us, bound by those uncoalesced loads; this one takes 92 us, bound by
+// the issue of about 85 vector instructions per wave, 32 of them the sum.
+// Here a block takes the features 16 at a time:
+// its rho column points are loaded once, coalesced, into LDS (pitch 20
+// floats: the 16-byte reads of 16 lanes cover every bank once), the next 16
+// features being loaded before the current ones are used.  rho 16 and 32:
+// lane l holds feature l mod 16 of its row's point and the row_newbcast lane
+// move hands it to the row's 16 lanes, so the row points need no LDS read;
+// rho 8 (two rows in 16 lanes) reads them from LDS.  Features past d are 0
+// in both points and add an exact 0, so the sum has the bits of
+// pair_dist_rt.  LTM takes one contiguous range of lambda per XCD: the two
+// 64-byte pieces of an output line then meet in one L2.  ROUTE is the
+// strategy (the enum above).
+template <int RHO, int LAYOUT, int ROUTE>
+__global__ __launch_bounds__(RHO *RHO) void wide_cell_kernel(EdmArgs a, uint32_t lam0, int mode,
+                                                             uint32_t side, uint32_t nb) {
+  constexpr int F = 16;       // features per step
+  constexpr int PITCH = 20;   // floats per staged point
+  constexpr int NT = RHO * RHO;
+  constexpr int PER = RHO * F >= NT ? RHO * F / NT : 1;  // staged values per thread
+  constexpr bool ALL = RHO * F >= NT;                    // every thread stages
+  uint32_t bi, bj;
+  if constexpr (ROUTE == kLTM) {
+    g_lambda_uniform(lam0 + xcd_contiguous(blockIdx.x, gridDim.x), bi, bj);
+  } else if constexpr (ROUTE == kBB) {
+    bj = blockIdx.x;
+    bi = blockIdx.y;
+    if (bj > bi) return;
+  } else {
+    const uint32_t q = blockIdx.y / side;
+    const uint32_t lby = blockIdx.y - q * side;
+    bi = (mode == 0 ? q : 2 * q + 1) * side + lby;
+    bj = (mode == 0 ? q : 2 * q) * side + blockIdx.x;
+    if (bi >= nb || (mode == 0 && blockIdx.x > lby)) return;
+  }
+  const uint32_t tx = threadIdx.x, ty = threadIdx.y;
+  const uint32_t t = ty * RHO + tx;
+  const int d = a.d;
+  // the 32-bit block index keeps N below 92682 rho
+  const uint32_t N = (uint32_t)a.N, i0 = bi * RHO, j0 = bj * RHO;
+  const uint32_t ni = N - i0 < RHO ? N - i0 : RHO;  // points of the block that exist
+  const uint32_t nj = N - j0 < RHO ? N - j0 : RHO;
+  const float *__restrict__ Xi = a.X + i0 * a.ldx;
+  const float *__restrict__ Xj = a.X + j0 * a.ldx;
+  __shared__ __align__(16) float xc[2][RHO * PITCH];
+  __shared__ __align__(16) float xr[RHO == 8 ? 2 : 1][RHO == 8 ? RHO * PITCH : 4];
+
+  // the thread's staged elements: point (t + NT m) / 16, feature t mod 16;
+  // its row element: point ty (rho 8: as staged), the same feature
+  const uint32_t f = RHO == 8 ? t % F : tx % F;
+  uint64_t co[PER];
+#pragma unroll
+  for (int m = 0; m < PER; ++m) co[m] = (uint64_t)((RHO == 16 ? ty : t / F) + NT / F * m) * (uint64_t)a.ldx + f;
+  const uint64_t ro = RHO == 16 ? co[0] : (uint64_t)ty * (uint64_t)a.ldx + f;
+  const bool whole = ni == RHO && nj == RHO;
+  float cv[PER], rv[PER];
+  auto load = [&](int k0) {
+    if (whole && k0 + F <= d) {
+#pragma unroll
+      for (int m = 0; m < PER; ++m) {
+        if (ALL || t < RHO * F) {
+          cv[m] = Xj[co[m] + k0];
+          if constexpr (RHO == 8) rv[m] = Xi[co[m] + k0];
+        }
+      }
+      if constexpr (RHO != 8) rv[0] = Xi[ro + k0];
+      return;
+    }
+    const bool kok = k0 + (int)f < d;
+#pragma unroll
+    for (int m = 0; m < PER; ++m) {
+      const uint32_t p = t / F + NT / F * m;
+      cv[m] = kok && p < nj ? Xj[co[m] + k0] : 0.0f;
+      if constexpr (RHO == 8) rv[m] = kok && p < ni ? Xi[co[m] + k0] : 0.0f;
+    }
+    if constexpr (RHO != 8) rv[0] = kok && ty < ni ? Xi[ro + k0] : 0.0f;
+  };
+  load(0);
+  float s = 0.0f;
+  for (int k0 = 0, b = 0; k0 < d; k0 += F, b ^= 1) {
+    const float row = rv[0];
+    if (ALL || t < RHO * F) {
+#pragma unroll
+      for (int m = 0; m < PER; ++m) {
+        const uint32_t at = (t / F + NT / F * m) * PITCH + f;
+        xc[b][at] = cv[m];
+        if constexpr (RHO == 8) xr[b][at] = rv[m];
+      }
+    }
+    if (k0 + F < d) load(k0 + F);
+    // the other buffer's readers passed the previous step's barrier
+    __syncthreads();
+    const f4 *c = reinterpret_cast<const f4 *>(&xc[b][tx * PITCH]);
+    if constexpr (RHO == 8) {
+      const f4 *r = reinterpret_cast<const f4 *>(&xr[b][ty * PITCH]);
+#pragma unroll
+      for (int q = 0; q < F / 4; ++q) {
+        if (k0 + 4 * q < d) {
+          const f4 u = r[q], v = c[q];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float x = u[k], y = v[k];
+            const float tt = x - y;
+            s = __builtin_fmaf(tt, tt, s);
+          }
+        }
+      }
+    } else {
+      s = add_features<0>(s, row, c[0]);
+      if (k0 + 4 < d) s = add_features<4>(s, row, c[1]);
+      if (k0 + 8 < d) s = add_features<8>(s, row, c[2]);
+      if (k0 + 12 < d) s = add_features<12>(s, row, c[3]);
+    }
+  }
+  const float v = __builtin_amdgcn_sqrtf(s);
+  // cell (i0 + ty, j0 + tx): the block's first cell and a lane offset
+  // (packed: T(i0 + ty) = T(i0) + ty i0 + ty (ty + 1) / 2, ty i0 < 2^32)
+  float *__restrict__ o = a.D + out_index<LAYOUT>((uint64_t)i0, (uint64_t)j0, a.ldd);
+  uint64_t lo;
+  if constexpr (LAYOUT == kLayoutFull)
+    lo = (uint64_t)ty * (uint64_t)a.ldd + tx;
+  else
+    lo = ty * i0 + ((ty * (ty + 1)) >> 1) + tx;
+  if (bj < bi && ni == RHO)
+    o[lo] = v;
+  else if (ty < ni && j0 + tx <= i0 + ty)
+    o[lo] = v;
+}
+
+// ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
 
@@ -187,68 +351,113 @@ static void rec_shape(uint32_t nb, uint32_t &m, uint32_t &k) {
   }
 }
 
-template <int D, int LAYOUT, int MODE>
-static hipError_t launch_cell_t(int strategy, int rho, const EdmArgs &a,
-                                unsigned long long *counts) {
-  const dim3 blk(rho, rho);
-  const uint64_t lanes = (uint64_t)rho * rho;
+// The launches of the strategies whose blocks are rho x rho squares of
+// cells (LTM, BB, REC): go(route, grid, lam0, mode, side) makes one launch,
+// route an integral_constant of the strategy.
+template <class Go>
+static hipError_t launch_square_blocks(int strategy, int rho, const EdmArgs &a, Go go) {
   const uint64_t nb = (uint64_t)((a.N + rho - 1) / rho);
   // keep every launch below 2^32 work-items
-  const uint64_t max_blocks = (((uint64_t)1 << 32) - 1) / lanes;
+  const uint64_t max_blocks = (((uint64_t)1 << 32) - 1) / ((uint64_t)rho * rho);
   hipError_t e = hipSuccess;
   switch (strategy) {
     case kLTM: {
       const uint64_t T = nb * (nb + 1) / 2;
       for (uint64_t l0 = 0; l0 < T; l0 += max_blocks) {
         const uint64_t c = T - l0 < max_blocks ? T - l0 : max_blocks;
-        hipLaunchKernelGGL((ltm_cell_kernel<D, LAYOUT, MODE>), dim3((uint32_t)c), blk, 0,
-                           a.stream, a, (uint32_t)l0, counts);
+        go(std::integral_constant<int, kLTM>(), dim3((uint32_t)c), (uint32_t)l0, 0, 0u);
         if ((e = hipGetLastError()) != hipSuccess) return e;
       }
       return e;
     }
     case kBB:
-      hipLaunchKernelGGL((bb_cell_kernel<D, LAYOUT, MODE>), dim3((uint32_t)nb, (uint32_t)nb),
-                         blk, 0, a.stream, a, counts);
+      go(std::integral_constant<int, kBB>(), dim3((uint32_t)nb, (uint32_t)nb), 0u, 0, 0u);
       return hipGetLastError();
-    case kUTM: {
-      const uint64_t P = (uint64_t)a.N * (uint64_t)(a.N + 1) / 2;
-      const uint64_t blocks = (P + lanes - 1) / lanes;
-      for (uint64_t b0 = 0; b0 < blocks; b0 += max_blocks) {
-        const uint64_t c = blocks - b0 < max_blocks ? blocks - b0 : max_blocks;
-        hipLaunchKernelGGL((utm_cell_kernel<D, LAYOUT, MODE>), dim3((uint32_t)c), blk, 0,
-                           a.stream, a, b0 * lanes, counts);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-      }
-      return e;
-    }
-    case kRB: {
-      const int64_t rows = (a.N % 2 == 0) ? a.N + 1 : a.N;
-      const int64_t cols = (a.N % 2 == 0) ? a.N / 2 : a.N / 2 + 1;
-      const uint32_t gx = (uint32_t)((cols + rho - 1) / rho);
-      const uint32_t gy = (uint32_t)((rows + rho - 1) / rho);
-      if (gx == 0 || gy == 0) return hipSuccess;
-      hipLaunchKernelGGL((rb_cell_kernel<D, LAYOUT, MODE>), dim3(gx, gy), blk, 0, a.stream, a,
-                         counts);
-      return hipGetLastError();
-    }
     case kREC: {
       uint32_t m = 1, k = 0;
       rec_shape((uint32_t)nb, m, k);
-      hipLaunchKernelGGL((rec_cell_kernel<D, LAYOUT, MODE>), dim3(m, m << k), blk, 0, a.stream,
-                         a, 0, m, (uint32_t)nb, counts);
+      go(std::integral_constant<int, kREC>(), dim3(m, m << k), 0u, 0, m);
       if ((e = hipGetLastError()) != hipSuccess) return e;
       for (uint32_t lev = 0; lev < k; ++lev) {
         const uint32_t s = m << lev;
         const uint32_t squares = 1u << (k - 1 - lev);
-        hipLaunchKernelGGL((rec_cell_kernel<D, LAYOUT, MODE>), dim3(s, s * squares), blk, 0,
-                           a.stream, a, 1, s, (uint32_t)nb, counts);
+        go(std::integral_constant<int, kREC>(), dim3(s, s * squares), 0u, 1, s);
         if ((e = hipGetLastError()) != hipSuccess) return e;
       }
       return e;
     }
     default:
       return hipErrorInvalidValue;
+  }
+}
+
+// UTM and RB.
+template <int D, int LAYOUT, int MODE>
+static hipError_t launch_pair_blocks(int strategy, int rho, const EdmArgs &a,
+                                     unsigned long long *counts) {
+  const dim3 blk(rho, rho);
+  const uint64_t lanes = (uint64_t)rho * rho;
+  const uint64_t max_blocks = (((uint64_t)1 << 32) - 1) / lanes;
+  hipError_t e = hipSuccess;
+  if (strategy == kUTM) {
+    const uint64_t P = (uint64_t)a.N * (uint64_t)(a.N + 1) / 2;
+    const uint64_t blocks = (P + lanes - 1) / lanes;
+    for (uint64_t b0 = 0; b0 < blocks; b0 += max_blocks) {
+      const uint64_t c = blocks - b0 < max_blocks ? blocks - b0 : max_blocks;
+      hipLaunchKernelGGL((utm_cell_kernel<D, LAYOUT, MODE>), dim3((uint32_t)c), blk, 0,
+                         a.stream, a, b0 * lanes, counts);
+      if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    return e;
+  }
+  if (strategy != kRB) return hipErrorInvalidValue;
+  const int64_t rows = (a.N % 2 == 0) ? a.N + 1 : a.N;
+  const int64_t cols = (a.N % 2 == 0) ? a.N / 2 : a.N / 2 + 1;
+  const uint32_t gx = (uint32_t)((cols + rho - 1) / rho);
+  const uint32_t gy = (uint32_t)((rows + rho - 1) / rho);
+  if (gx == 0 || gy == 0) return hipSuccess;
+  hipLaunchKernelGGL((rb_cell_kernel<D, LAYOUT, MODE>), dim3(gx, gy), blk, 0, a.stream, a,
+                     counts);
+  return hipGetLastError();
+}
+
+template <int D, int LAYOUT, int MODE>
+static hipError_t launch_cell_t(int strategy, int rho, const EdmArgs &a,
+                                unsigned long long *counts) {
+  if (strategy == kUTM || strategy == kRB)
+    return launch_pair_blocks<D, LAYOUT, MODE>(strategy, rho, a, counts);
+  const uint32_t nb = (uint32_t)((a.N + rho - 1) / rho);
+  return launch_square_blocks(
+      strategy, rho, a, [&](auto route, dim3 grid, uint32_t lam0, int mode, uint32_t side) {
+        const dim3 blk(rho, rho);
+        if constexpr (route == kLTM)
+          hipLaunchKernelGGL((ltm_cell_kernel<D, LAYOUT, MODE>), grid, blk, 0, a.stream, a, lam0,
+                             counts);
+        else if constexpr (route == kBB)
+          hipLaunchKernelGGL((bb_cell_kernel<D, LAYOUT, MODE>), grid, blk, 0, a.stream, a, counts);
+        else
+          hipLaunchKernelGGL((rec_cell_kernel<D, LAYOUT, MODE>), grid, blk, 0, a.stream, a, mode,
+                             side, nb, counts);
+      });
+}
+
+template <int RHO, int LAYOUT>
+static hipError_t launch_wide_t(int strategy, const EdmArgs &a) {
+  const uint32_t nb = (uint32_t)((a.N + RHO - 1) / RHO);
+  return launch_square_blocks(
+      strategy, RHO, a, [&](auto route, dim3 grid, uint32_t lam0, int mode, uint32_t side) {
+        hipLaunchKernelGGL((wide_cell_kernel<RHO, LAYOUT, route>), grid, dim3(RHO, RHO), 0, a.stream,
+                           a, lam0, mode, side, nb);
+      });
+}
+
+template <int LAYOUT>
+static hipError_t launch_wide(int strategy, int rho, const EdmArgs &a) {
+  switch (rho) {
+    case 8: return launch_wide_t<8, LAYOUT>(strategy, a);
+    case 16: return launch_wide_t<16, LAYOUT>(strategy, a);
+    case 32: return launch_wide_t<32, LAYOUT>(strategy, a);
+    default: return hipErrorInvalidValue;
   }
 }
 
@@ -259,7 +468,15 @@ static hipError_t launch_cell_layout(int strategy, int rho, const EdmArgs &a) {
     case 2: return launch_cell_t<2, LAYOUT, kModeStore>(strategy, rho, a, nullptr);
     case 3: return launch_cell_t<3, LAYOUT, kModeStore>(strategy, rho, a, nullptr);
     case 4: return launch_cell_t<4, LAYOUT, kModeStore>(strategy, rho, a, nullptr);
-    default: return launch_cell_t<0, LAYOUT, kModeStore>(strategy, rho, a, nullptr);
+    default: break;
+  }
+  // more than four features: the square-block strategies stage the points;
+  // UTM and RB blocks are not squares of cells (a block of UTM is a run of
+  // pairs, one of RB may straddle the turned-over part)
+  switch (strategy) {
+    case kUTM:
+    case kRB: return launch_pair_blocks<0, LAYOUT, kModeStore>(strategy, rho, a, nullptr);
+    default: return launch_wide<LAYOUT>(strategy, rho, a);
   }
 }
 
