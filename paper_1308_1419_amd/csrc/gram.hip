@@ -15,12 +15,20 @@
 // Two kernels walk the triangle by g(lambda) (Sec. II-A, Eq. (2)) and
 // compute every 32 x 32 block with the same instructions in the same order,
 // so their outputs are equal bit for bit:
-//   - gram_tile_kernel: a work-group of eight waves owns one row half (two
-//     128 x 128 tiles side by side) of a 256 x 256 tile;
-//   - gram_strip_kernel: a work-group of four waves owns a 32-row strip of
-//     a 256 x 256 tile, the strips of a tile row taken strip by strip across
-//     the row (the order of the FP32 strips), so that the writes in flight
-//     stay in a compact window of the packed output.
+//   - gram_block_kernel: eight waves on 128 x 256 cells, each wave 64 x 64,
+//     so an operand byte read from LDS feeds twice the products of a 32 x 32
+//     wave block;
+//   - gram_strip_kernel: eight waves on a 32-row strip of a 256 x 256 tile,
+//     the strips of a tile row taken strip by strip across the row (the
+//     order of the FP32 strips), so that the writes in flight stay in a
+//     compact window of the packed output and small N makes more
+//     work-groups.
+// Measured (us, blocks / strips, prologue included): N = 100000, d = 64
+// 4295 / 4425 (BF16), 5290 / 5174 (split); N = 50000, d = 256 1694 / 1937;
+// N = 30011, d = 200 split 824 / 897; N = 2000, d = 100 19.4 / 12.6.  The
+// autotuner times both.  With row-major operands, staged through LDS in the
+// strips and loaded by every lane on its own in 128 x 128 tiles, the same
+// sizes took, in the faster of the two, 4403, 6647, 2946, 1872 and 15.7 us.
 //
 // Split mode (precision BF16X3): each point is held as x = hi + lo with
 // hi = bf16(x) and lo = bf16(x - hi) (x - hi is exact in FP32, and hi + lo
@@ -36,7 +44,6 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-constexpr int kGramTile = 128;  // tile kernel: 128 x 128 per eight waves
 constexpr int kGramPad = 256;   // operand rows are padded to this
 constexpr float kGramTheta = 0.25f;
 
@@ -49,59 +56,81 @@ __device__ __forceinline__ uint16_t bf16_rne(float f) {
 
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
+// The operands sit in memory as the MFMA instruction takes them.  A fragment
+// holds 32 points x 16 features, 1 KB: lane l = p mod 32 + 32 h of the wave
+// that multiplies it finds the features 8 h .. 8 h + 7 of point p at
+// 16-byte chunk l.  Fragment (p / 32, k / 16) is number (p / 32) KS + k / 16
+// (KS = KP / 16), so a wave loads one with a single 1 KB contiguous
+// instruction, into registers or LDS alike, and reads it back from LDS
+// without bank conflicts.
+constexpr int kFragElems = 512;
+
 // The BF16 copy (zero padded) and the squared norms of the represented
-// points; with Xlo != nullptr also the low parts.  A thread converts one
-// 8-feature chunk of one point and writes it as one 16-byte store, so
-// consecutive threads write consecutive chunks.  A work-group takes
-// ppb = 256 / cpp whole points (cpp = KP / 8 chunks per point; a point with
-// more than 256 chunks takes a work-group alone, its threads stepping by
-// 256 chunks); the chunk partial sums of a point are then added in chunk
-// order by its first thread.
+// points; with Xlo != nullptr also the low parts.  A work-group takes 32
+// points: thread t converts the 8-feature chunks t / 32, t / 32 + 8, ... of
+// point t mod 32 and writes each as one 16-byte store (a wave writes two
+// chunks of 32 points, 1 KB).  VEC: whole chunks are read as two 16-byte
+// loads.  The chunk sums of a point are kept by chunk modulo 256 and added
+// in that order.
+template <bool VEC>
 __global__ __launch_bounds__(256) void gram_prologue_kernel(const float *__restrict__ X, int64_t N, int d,
                                                             int64_t ldx, uint16_t *__restrict__ Xb,
                                                             uint16_t *__restrict__ Xlo,
-                                                            float *__restrict__ nrm, int64_t Npad,
-                                                            int KP) {
+                                                            float *__restrict__ nrm, int KP) {
   typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-  __shared__ float part[256];
+  extern __shared__ float part[];  // [min(KP / 8, 256)][32]
   const int cpp = KP >> 3;
-  const int ppb = cpp <= 256 ? 256 / cpp : 1;
   const int t = threadIdx.x;
-  const int pl = cpp <= 256 ? t / cpp : 0;  // the thread's point within the work-group
-  const int64_t p = (int64_t)blockIdx.x * ppb + pl;
-  const bool live = pl < ppb && p < Npad;
-  float s = 0.0f;
-  if (live) {
-    for (int c = cpp <= 256 ? t - pl * cpp : t; c < cpp; c += 256) {
-      uint16_t hb[8], lb[8];
+  const int pl = t & 31;
+  const int64_t p = (int64_t)blockIdx.x * 32 + pl;
+  const float *__restrict__ x = X + p * ldx;
+  uint16_t *__restrict__ hi = Xb + (int64_t)blockIdx.x * (KP >> 4) * kFragElems + pl * 8;
+  uint16_t *__restrict__ lp =
+      Xlo != nullptr ? Xlo + (int64_t)blockIdx.x * (KP >> 4) * kFragElems + pl * 8 : nullptr;
+  for (int c = t >> 5; c < cpp; c += 8) {
+    float v[8];
+    if (VEC && p < N && 8 * c + 8 <= d) {
+      const f4 q0 = *reinterpret_cast<const f4 *>(x + 8 * c);
+      const f4 q1 = *reinterpret_cast<const f4 *>(x + 8 * c + 4);
 #pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const int k = 8 * c + u;
-        const float v = (p < N && k < d) ? X[p * ldx + k] : 0.0f;
-        hb[u] = bf16_rne(v);
-        float r = bf16_to_f32(hb[u]);
-        if (Xlo != nullptr) {
-          lb[u] = bf16_rne(v - r);
-          r += bf16_to_f32(lb[u]);
-        }
-        s = __builtin_fmaf(r, r, s);
+      for (int u = 0; u < 4; ++u) {
+        v[u] = q0[u];
+        v[4 + u] = q1[u];
       }
-      u4 h, lo;
+    } else {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        h[e] = (uint32_t)hb[2 * e] | ((uint32_t)hb[2 * e + 1] << 16);
-        lo[e] = (uint32_t)lb[2 * e] | ((uint32_t)lb[2 * e + 1] << 16);
-      }
-      *reinterpret_cast<u4 *>(Xb + p * KP + 8 * c) = h;
-      if (Xlo != nullptr) *reinterpret_cast<u4 *>(Xlo + p * KP + 8 * c) = lo;
+      for (int u = 0; u < 8; ++u) v[u] = (p < N && 8 * c + u < d) ? x[8 * c + u] : 0.0f;
     }
+    uint16_t hb[8], lb[8];
+    const int slot = (c & 255) * 32 + pl;
+    float s = c < 256 ? 0.0f : part[slot];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      hb[u] = bf16_rne(v[u]);
+      float r = bf16_to_f32(hb[u]);
+      if (Xlo != nullptr) {
+        lb[u] = bf16_rne(v[u] - r);
+        r += bf16_to_f32(lb[u]);
+      }
+      s = __builtin_fmaf(r, r, s);
+    }
+    part[slot] = s;
+    u4 h, lo;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      h[e] = (uint32_t)hb[2 * e] | ((uint32_t)hb[2 * e + 1] << 16);
+      lo[e] = (uint32_t)lb[2 * e] | ((uint32_t)lb[2 * e + 1] << 16);
+    }
+    // chunk c: half c mod 2 of fragment c / 2
+    const int64_t at = (int64_t)(c >> 1) * kFragElems + (c & 1) * 256;
+    *reinterpret_cast<u4 *>(hi + at) = h;
+    if (Xlo != nullptr) *reinterpret_cast<u4 *>(lp + at) = lo;
   }
-  part[t] = s;
   __syncthreads();
-  if (live && (cpp > 256 ? t == 0 : t == pl * cpp)) {
+  if (t < 32) {
     float n = 0.0f;
     const int m = cpp < 256 ? cpp : 256;
-    for (int c = 0; c < m; ++c) n += part[t + c];
+    for (int c = 0; c < m; ++c) n += part[c * 32 + t];
     nrm[p] = n;
   }
 }
@@ -132,53 +161,6 @@ __device__ __forceinline__ float exact_dist(const float *__restrict__ X, int64_t
   return __builtin_amdgcn_sqrtf(q);
 }
 
-// The products of NB 32 x 32 blocks sharing one 32-row block of A: block b
-// takes the 32 points starting at col[b].  Lane l supplies row (l % 32) of
-// a 32-row block and the 8 features [8 (l / 32), 8 (l / 32) + 8) of each
-// 16-feature step; B uses the same assignment for its points, so the
-// product is x_i . x_j.  Blocks with live[b] false are left at zero.  The
-// steps run in increasing feature order and, in split mode, each step adds
-// lo.hi', hi.lo', hi.hi' in that order: every kernel that calls this gets
-// the same bits for the same block.
-template <bool SPLIT, int KPC, int NB>
-__device__ __forceinline__ void gram_products(const GramArgs &a, int KP, int64_t row, const int64_t (&col)[NB],
-                                              const bool (&live)[NB], f32x16 (&acc)[NB]) {
-  const int l = threadIdx.x & 63;
-  const int lr = l & 31;
-  const int lk = (l >> 5) * 8;
-  const uint16_t *__restrict__ Xb = a.Xb;
-  const uint16_t *__restrict__ Xl = a.Xlo;
-#pragma unroll
-  for (int b = 0; b < NB; ++b)
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[b][v] = 0.0f;
-  auto kstep = [&](int k) {
-    const int64_t ao = (row + lr) * KP + k + lk;
-    const bf16x8 av = *reinterpret_cast<const bf16x8 *>(Xb + ao);
-    bf16x8 al;
-    if constexpr (SPLIT) al = *reinterpret_cast<const bf16x8 *>(Xl + ao);
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      if (live[b]) {
-        const int64_t bo = (col[b] + lr) * KP + k + lk;
-        const bf16x8 bv = *reinterpret_cast<const bf16x8 *>(Xb + bo);
-        if constexpr (SPLIT) {
-          const bf16x8 bl = *reinterpret_cast<const bf16x8 *>(Xl + bo);
-          acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bv, acc[b], 0, 0, 0);
-          acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bl, acc[b], 0, 0, 0);
-        }
-        acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[b], 0, 0, 0);
-      }
-    }
-  };
-  if constexpr (KPC != 0) {
-#pragma unroll
-    for (int k = 0; k < KPC; k += 16) kstep(k);
-  } else {
-    for (int k = 0; k < KP; k += 16) kstep(k);
-  }
-}
-
 // Accumulator v of a 32 x 32 block holds row (v/4)*8 + (l/32)*4 + v%4 of
 // the block and column l % 32.
 __device__ __forceinline__ int acc_row(int v, int l) { return (v >> 2) * 8 + (l >> 5) * 4 + (v & 3); }
@@ -192,187 +174,185 @@ __device__ __forceinline__ float gram_value(float acc, float ni, float nj) {
   return G <= kGramTheta * sn ? -1.0f : __builtin_amdgcn_sqrtf(G);
 }
 
-// (i(i+1)/2 + c) mod 4 for a row i that is a multiple of 32 plus rr and a
-// column c that is a multiple of 128: i(i+1)/2 mod 4 has period 8 in i.
-__device__ __forceinline__ int row_shift(int rr) {
-  const int m = rr & 7;
-  return ((m * (m + 1)) >> 1) & 3;
+// One 1 KB fragment from global memory straight into LDS: lane l's 16 bytes
+// land at dst + 16 l.
+__device__ __forceinline__ void load_fragment(const uint16_t *src, unsigned char *dst) {
+  __builtin_amdgcn_global_load_lds(
+      (const __attribute__((address_space(1))) void *)(src + (threadIdx.x & 63) * 8),
+      (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
+}
+
+// Lane l's part of fragment f of an LDS area.
+__device__ __forceinline__ bf16x8 lds_fragment(const unsigned char *ops, int f) {
+  return *reinterpret_cast<const bf16x8 *>(ops + f * 1024 + (threadIdx.x & 63) * 16);
+}
+
+// One k-step of a 32 x 32 block; split: lo.hi', hi.lo', hi.hi' in that
+// order.  Steps run in increasing feature order in every kernel, so a block
+// has the same bits wherever it is computed.
+template <bool SPLIT>
+__device__ __forceinline__ f32x16 gram_step(f32x16 acc, bf16x8 ah, bf16x8 al, bf16x8 bh, bf16x8 bl) {
+  if constexpr (SPLIT) {
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bh, acc, 0, 0, 0);
+    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bl, acc, 0, 0, 0);
+  }
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, bh, acc, 0, 0, 0);
 }
 
 // ---------------------------------------------------------------------------
-// tile kernel: eight waves, two 128 x 128 tiles side by side
+// block kernel: eight waves, 128 x 256 cells
 // ---------------------------------------------------------------------------
 
-// Each wave owns 32 whole rows of the 128 x 128 tile: four 32 x 32
-// accumulators (one per 32-column block).  Its distances go, 16 rows at a
-// time, through a wave-private LDS slice and are written as packed rows with
-// 16-byte stores; no work-group barrier is needed, so the waves run
-// independently.
-//
-// Store layout: a half-wave writes one 128-cell row segment.  Packed row i's
-// segment [col0, col0 + 128) starts sh = (D / 4 + i(i+1)/2 + col0) mod 4
-// positions past a 16-byte boundary (D / 4: the output's own offset in
-// floats); lane h stores the aligned chunk at columns col0 - sh + 4h .. + 3,
-// read from LDS at that shift.  The cells of the two partial chunks at the
-// ends of each segment (the neighbouring tiles write the rest of those
-// chunks) are gathered one row per lane and written with four instructions
-// per 16 rows: single-lane stores per row would multiply the store
-// instruction count several times over.  Diagonal and edge rows go cell by
-// cell.
-constexpr int kGramRows = 16;  // rows staged per step and wave
+// Eight waves as 2 x 4, each on 64 x 64 cells (2 x 2 MFMA blocks).  Stage s
+// holds the fragments of the work-group's 12 point blocks for two k-steps
+// (split: the high and low parts of one), 24 KB, loaded straight into LDS
+// two stages ahead of their use: three buffers, one barrier a stage, two
+// work-groups per CU.
+constexpr int kBlkRows = 128;
+constexpr int kBlkFrags = 2 * (kBlkRows / 32 + 8);  // per stage
+constexpr int kBlkStage = kBlkFrags * 1024;
+constexpr int kBlkLoads = kBlkFrags / 8;            // per wave and stage
+static_assert(8 * 32 * 64 * 4 <= 3 * kBlkStage, "the staged output overlays the operands");
 
-template <bool SPLIT, int KPC, bool COUNT>
-__global__ __launch_bounds__(512, SPLIT ? 3 : 4) void gram_tile_kernel(GramArgs a, uint32_t lam0,
-                                                                      uint32_t nblk) {
-  // Eight waves: the two side-by-side 128 x 128 tiles (I, 2 J2) and
-  // (I, 2 J2 + 1) that form one row half, I = 2 I2 + wg mod 2, of the
-  // 256 x 256 tile (I2, J2) = g(wg / 2), so each row is written as a 1 KB
-  // segment.  Each XCD takes one contiguous range of wg: neighbouring tiles
-  // share the partial 16-byte chunks (and lines) at the ends of their row
-  // segments, which then combine in one L2, and they share their BF16 row
-  // block.
-  const uint32_t wg = lam0 + xcd_contiguous(blockIdx.x, nblk);
-  uint32_t I2, J2;
-  g_lambda(wg >> 1, I2, J2);
-  const int wl = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint32_t I = 2 * I2 + (wg & 1);
-  uint32_t J = 2 * J2 + (wl >> 2);
-  I = __builtin_amdgcn_readfirstlane(I);  // uniform: keep the tile origin scalar
-  J = __builtin_amdgcn_readfirstlane(J);
-  // the upper right tile of a diagonal 256 x 256 tile, or rows past N
-  if (J > I || (int64_t)I * kGramTile >= a.N) return;
-  const int w = wl & 3;  // the wave's 32-row block of its 128 x 128 tile
+template <bool SPLIT, bool COUNT>
+__global__ __launch_bounds__(512, 4) void gram_block_kernel(GramArgs a, uint32_t w0, uint32_t nblk) {
+  __shared__ __align__(16) unsigned char ops[3 * kBlkStage];
+  const uint32_t w = w0 + xcd_contiguous(blockIdx.x, nblk);
+  // tile row I2 of 256 rows holds 2 (I2 + 1) work-groups: the upper 128
+  // rows across all its tiles, then the lower ones
+  uint32_t I2, Jt;
+  g_lambda_uniform(w >> 1, I2, Jt);
+  const uint32_t u = 2 * Jt + (w & 1);
+  const uint32_t half = u > I2 ? 1 : 0;
+  const uint32_t J = u - half * (I2 + 1);
+  const int64_t N = a.N;
+  const int64_t r0 = (int64_t)I2 * 256 + half * kBlkRows;
+  const int64_t c0 = (int64_t)J * 256;
+  if (r0 >= N) return;  // uniform
+  const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l = threadIdx.x & 63;
   const int lr = l & 31;
-  const int64_t N = a.N;
-  const int64_t row0 = (int64_t)I * kGramTile;
-  const int64_t col0 = (int64_t)J * kGramTile;
-  const int64_t rw = row0 + 32 * w;  // this wave's first row
-  const bool diag = I == J;
-  const int KP = KPC ? KPC : a.KP;
-  const int bsh = (int)((reinterpret_cast<uintptr_t>(a.D) >> 2) & 3);
-  auto shift = [&](int rr) { return (row_shift(rr) + bsh) & 3; };
+  const int KS = a.KP >> 4;
+  const int wr = q >> 2, wc = q & 3;
+  const int stages = SPLIT ? KS : (KS + 1) >> 1;
 
-  float nr[16];
+  // fragment f of a stage: point block f / 2 (rows first), f odd: the second
+  // k-step (absent when KS is odd and the stage the last) or the low part
+  auto load_stage = [&](int s) {
+    unsigned char *buf = ops + (s % 3) * kBlkStage;
 #pragma unroll
-  for (int v = 0; v < 16; ++v) nr[v] = a.nrm[rw + acc_row(v, l)];
-  float nc[4];
+    for (int m = 0; m < kBlkLoads; ++m) {
+      const int f = q + 8 * m;
+      const int pb = f >> 1, odd = f & 1;
+      const int64_t g = pb < kBlkRows / 32 ? (r0 >> 5) + pb : (c0 >> 5) + (pb - kBlkRows / 32);
+      const uint16_t *src = (SPLIT && odd) ? a.Xlo : a.Xb;
+      int ks = SPLIT ? s : 2 * s + odd;
+      ks = ks < KS ? ks : KS - 1;  // (loaded, not used)
+      load_fragment(src + (g * KS + ks) * kFragElems, buf + f * 1024);
+    }
+  };
+  f32x16 acc[2][2];
 #pragma unroll
-  for (int bj = 0; bj < 4; ++bj) nc[bj] = a.nrm[col0 + bj * 32 + lr];
+  for (int x = 0; x < 2; ++x)
+#pragma unroll
+    for (int y = 0; y < 2; ++y)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) acc[x][y][v] = 0.0f;
 
-  // on a diagonal tile, column blocks right of this wave's rows are above
-  // the diagonal
-  int64_t cols[4];
-  bool live[4];
+  load_stage(0);
+  if (stages > 1) load_stage(1);
+  for (int s = 0; s < stages; ++s) {
+    // this wave's share of stage s has landed (the loads complete in order)
+    if (s + 1 < stages)
+      __builtin_amdgcn_s_waitcnt(0x0F70 | kBlkLoads);  // vmcnt(kBlkLoads)
+    else
+      __builtin_amdgcn_s_waitcnt(0x0F70);
+    // ... and every wave's, and stage s - 1 is read (no fence: it would wait
+    // for the loads in flight; the empty asm keeps the LDS reads below)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    if (s + 2 < stages) load_stage(s + 2);
+    const unsigned char *buf = ops + (s % 3) * kBlkStage;
+    bf16x8 av[2][2], bv[2][2];  // [block][k-step or part]
 #pragma unroll
-  for (int bj = 0; bj < 4; ++bj) {
-    cols[bj] = col0 + bj * 32;
-    live[bj] = !diag || bj <= w;
+    for (int x = 0; x < 2; ++x)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        av[x][h] = lds_fragment(buf, 2 * (2 * wr + x) + h);
+        bv[x][h] = lds_fragment(buf, 2 * (kBlkRows / 32 + 2 * wc + x) + h);
+      }
+    if constexpr (SPLIT) {
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+#pragma unroll
+          for (int y = 0; y < 2; ++y)
+            acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[x][p == 0], bv[y][p == 1], acc[x][y],
+                                                                0, 0, 0);
+    } else {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)
+        if (2 * s + h < KS)
+#pragma unroll
+          for (int x = 0; x < 2; ++x)
+#pragma unroll
+            for (int y = 0; y < 2; ++y)
+              acc[x][y] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av[x][h], bv[y][h], acc[x][y], 0, 0, 0);
+    }
   }
-  f32x16 acc[4];
-  gram_products<SPLIT, KPC, 4>(a, KP, rw, cols, live, acc);
+  __syncthreads();  // the operands are read
 
-  // stage row rr holds column c at position c + shift(rr); the stored
-  // chunks are then aligned 16-byte LDS reads without bank conflicts
-  __shared__ __align__(16) float stage[8][kGramRows][kGramTile + 4];
-  float(*st)[kGramTile + 4] = stage[wl];
-  float *__restrict__ out = a.D;
-  const int h = l & 31;
-  const bool full_rows = !diag && row0 + kGramTile <= N;
+  // output: 32 rows x 64 columns at a time through the wave's own 8 KB of
+  // LDS, then whole rows of 64 cells (256 contiguous bytes per store)
+  const int64_t cw = c0 + 64 * wc;
+  float *st = reinterpret_cast<float *>(ops) + q * 32 * 64;
+  float nc[2];
+#pragma unroll
+  for (int y = 0; y < 2; ++y) nc[y] = a.nrm[cw + 32 * y + lr];
   uint32_t nrec = 0;
 #pragma unroll
-  for (int vh = 0; vh < 2; ++vh) {
-    // v in [8 vh, 8 vh + 8) are the rows 16 vh .. +15
-    bool any = false;
+  for (int x = 0; x < 2; ++x) {
+    const int64_t rw = r0 + 64 * wr + 32 * x;
+    if (rw >= N || cw > rw + 31) continue;  // no cell of the triangle (uniform)
+    uint32_t flag[2] = {0, 0};
 #pragma unroll
-    for (int bj = 0; bj < 4; ++bj) {
+    for (int v = 0; v < 16; ++v) {
+      const int rr = acc_row(v, l);
+      const float ni = a.nrm[rw + rr];
 #pragma unroll
-      for (int v = 8 * vh; v < 8 * vh + 8; ++v) {
-        const int rr = acc_row(v, l) - 16 * vh;
-        const float g = gram_value(acc[bj][v], nr[v], nc[bj]);
-        any |= g < 0.0f;
-        st[rr][bj * 32 + lr + shift(rr)] = g;
+      for (int y = 0; y < 2; ++y) {
+        const float e = acc[x][y][v];
+        const float g = gram_value(e, ni, nc[y]);
+        flag[y] |= (uint32_t)(g < 0.0f) << v;
+        st[rr * 64 + 32 * y + lr] = g < 0.0f ? 0.0f : g;
       }
     }
-    if (any) {
-      // rare: the diagonal and near-duplicate pairs, exact FP32 difference
-#pragma unroll
-      for (int bj = 0; bj < 4; ++bj) {
-#pragma unroll
-        for (int v = 8 * vh; v < 8 * vh + 8; ++v) {
-          const int rr = acc_row(v, l) - 16 * vh;
-          const int c = bj * 32 + lr + shift(rr);
-          if (st[rr][c] < 0.0f) {
-            const int64_t i = rw + 16 * vh + rr;
-            const int64_t j = col0 + bj * 32 + lr;
-            const bool cell = i < N && j <= i;
-            if (COUNT) nrec += cell;
-            st[rr][c] = cell ? exact_dist(a.X, a.ldx, a.d, i, j) : 0.0f;
-          }
+    if ((flag[0] | flag[1]) != 0) {
+#pragma unroll 1
+      for (int m = 0; m < 32; ++m) {
+        const int y = m >> 4, v = m & 15;
+        if (((y ? flag[1] : flag[0]) >> v) & 1u) {
+          const int rr = acc_row(v, l);
+          const int64_t i = rw + rr, j = cw + 32 * y + lr;
+          const bool cell = i < N && j <= i;
+          if (COUNT) nrec += cell;
+          st[rr * 64 + 32 * y + lr] = cell ? exact_dist(a.X, a.ldx, a.d, i, j) : 0.0f;
         }
       }
     }
-    // the wave reads back its own LDS writes: no barrier needed
-    if (full_rows) {
-      // Row rw + m (m < 32) starts at T(rw) + col0 + m rw + m(m+1)/2: a
-      // uniform base and a 32-bit offset (m rw < 32 N < 2^30 under the
-      // 32-bit tile index), with the row's shift shift(m) (rw is a multiple
-      // of 32, so T(rw) and m rw add nothing mod 4).
-      float *__restrict__ outw = out + tri64((uint64_t)rw) + (uint64_t)col0;
-      const uint32_t rw32 = (uint32_t)rw;
-      auto row_off = [&](uint32_t m) { return m * rw32 + ((m * (m + 1)) >> 1); };
-      // cell offset -> address as a 32-bit byte offset from the uniform base
-      auto at = [&](uint32_t e) {
-        return reinterpret_cast<float *>(reinterpret_cast<char *>(outw) + e * 4u);
-      };
-      // whole aligned chunks, two rows per instruction
-#pragma unroll 2
-      for (int p = 0; p < kGramRows / 2; ++p) {
-        const int r = 2 * p + (l >> 5);
-        const uint32_t m = 16 * vh + r;
-        const int sh = shift(r);
-        if (h > 0 || sh == 0) {
-          const f4 v4 = *reinterpret_cast<const f4 *>(&st[r][4 * h]);
-          f4 *dst = reinterpret_cast<f4 *>(at(row_off(m) - sh + 4 * h));
-          // BF16 form: plain stores (6.3 against 7.0 ms with non-temporal
-          // ones); the split form keeps non-temporal stores (8.4 against
-          // 9.3 ms with plain ones)
-          if constexpr (SPLIT)
-            __builtin_nontemporal_store(v4, dst);
-          else
-            *dst = v4;
-        }
-      }
-      // the partial chunks at both ends of every row: the 4 - sh head cells
-      // (columns 0 .. 3 - sh) and the sh tail cells (columns 128 - sh .. 127),
-      // one row per lane, four instructions for all 16 rows
-      if (l < kGramRows) {
-        const uint32_t m = 16 * vh + l;
-        const int sh = shift(l);
-        if (sh != 0) {
-          const uint32_t o0 = row_off(m);
-#pragma unroll
-          for (int q = 0; q < 4; ++q) {
-            const int c = q < 4 - sh ? q : kGramTile - 4 + q;
-            // plain (cached) store: the neighbouring tile writes the rest
-            // of this 16-byte chunk, and the two halves then meet in L2
-            // instead of reaching HBM as two partial line writes
-            *at(o0 + c) = st[l][c + sh];
-          }
-        }
-      }
+    __builtin_amdgcn_wave_barrier();  // the wave reads its own LDS writes
+    // row rw + r starts at T(rw) + r rw + r (r + 1) / 2
+    float *__restrict__ o = a.D + tri64((uint64_t)rw) + (uint64_t)cw + l;
+    const uint32_t rwu = (uint32_t)rw;
+    if (cw + 63 <= rw && rw + 32 <= N) {
+#pragma unroll 8
+      for (uint32_t r = 0; r < 32; ++r) o[r * rwu + ((r * (r + 1)) >> 1)] = st[r * 64 + l];
     } else {
-      for (int p = 0; p < kGramRows / 2; ++p) {
-        const int r = 2 * p + (l >> 5);
-        const int64_t i = rw + 16 * vh + r;
-        if (i >= N) continue;
-        const uint64_t first = tri64((uint64_t)i) + (uint64_t)col0;
-        const int sh = shift(r);
-        const int64_t jmax = (diag ? i : N - 1) - col0;
-        for (int c = h; c < kGramTile; c += 32)
-          if (c <= jmax) __builtin_nontemporal_store(st[r][c + sh], out + first + c);
-      }
+      for (uint32_t r = 0; r < 32; ++r)
+        if (rw + r < N && cw + l <= rw + r) o[r * rwu + ((r * (r + 1)) >> 1)] = st[r * 64 + l];
     }
+    __builtin_amdgcn_wave_barrier();
   }
   if (COUNT && nrec) atomicAdd(a.rec_count, (unsigned long long)nrec);
 }
@@ -389,30 +369,24 @@ __global__ __launch_bounds__(512, SPLIT ? 3 : 4) void gram_tile_kernel(GramArgs 
 // compact window of addresses) while a group's BF16 column points stay in
 // L2 across its 8 strips.
 //
-// Operands: the strip's 32 row points and 256 column points are staged in
-// LDS, 128 bytes per point and pass (64 BF16 features, or 32 high and 32
-// low parts in split mode; larger feature counts take several passes), by
-// 16-byte loads straight into LDS when every pass is full, else by
-// coalesced 16-byte loads through registers.  The 16-byte chunk c of staged row r sits at
-// chunk c ^ ((r / 2) mod 8) of its row, so that both the coalesced writes
-// and the MFMA operand reads (32 rows, one chunk each) hit every LDS bank
-// once per 16 lanes.  Wave q computes the 32 x 32 block of columns
-// [32 q, 32 q + 32) with the products of gram_products in the same order.
+// Operands: wave q computes the 32 x 32 block of columns [32 q, 32 q + 32)
+// and is the only one to use their fragments, so it loads those straight
+// into registers; the fragments of the 32 row points, which all eight waves
+// use, go to LDS, as many k-steps a pass as the area holds.  A work-group's
+// loads are thus one round up to 256 features (split) or 512.
 //
 // Output: the distances of the strip are staged in LDS (over the operand
 // area) and each wave writes whole packed rows q, q + 8, q + 16, q + 24:
 // lane l owns columns l + 64 c and every 4-byte store instruction writes 256
-// contiguous bytes.  The LDS footprint (37 KB) leaves four work-groups per
+// contiguous bytes.  The LDS footprint (33 KB) leaves four work-groups per
 // CU.
 constexpr int kStripRows = 32;
 constexpr int kStripsPerTile = 256 / kStripRows;
 constexpr int kStripWaves = 8;
-constexpr int kStripOpRows = kStripRows + 256;  // staged operand rows
-constexpr int kStripOpBytes = 128;              // bytes per staged row and pass
-constexpr int kStripPitch = 260;                // floats per staged output row
+constexpr int kStripPitch = 260;  // floats per staged output row
+constexpr int kStripBytes = kStripRows * kStripPitch * 4;
+constexpr int kStripFrags = kStripBytes / 1024;  // fragments that fit the area
 constexpr uint32_t kStripGroup = 8;
-static_assert(kStripRows * kStripPitch * 4 <= kStripOpRows * kStripOpBytes,
-              "the staged output overlays the operand area");
 
 __device__ __forceinline__ void strip_order(uint32_t w, uint32_t group, uint32_t &I, uint32_t &k,
                                             uint32_t &J) {
@@ -436,16 +410,10 @@ __device__ __forceinline__ void strip_order(uint32_t w, uint32_t group, uint32_t
   }
 }
 
-// Byte offset of 16-byte chunk c of staged operand row r.
-__device__ __forceinline__ int strip_chunk(int r, int c) {
-  return r * kStripOpBytes + ((c ^ ((r >> 1) & 7)) << 4);
-}
-
 template <bool SPLIT, int KPC, bool COUNT>
-__global__ __launch_bounds__(kStripWaves * 64) void gram_strip_kernel(GramArgs a, uint32_t w0,
-                                                                      uint32_t nblk) {
-  typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-  __shared__ __align__(16) unsigned char ops[kStripOpRows * kStripOpBytes];
+__global__ __launch_bounds__(kStripWaves * 64, 8) void gram_strip_kernel(GramArgs a, uint32_t w0,
+                                                                         uint32_t nblk) {
+  __shared__ __align__(16) unsigned char ops[kStripBytes];
   __shared__ float nrow[kStripRows];
   float *st = reinterpret_cast<float *>(ops);  // after the products
   const uint32_t w = w0 + xcd_contiguous(blockIdx.x, nblk);
@@ -460,82 +428,54 @@ __global__ __launch_bounds__(kStripWaves * 64) void gram_strip_kernel(GramArgs a
   const int q = __builtin_amdgcn_readfirstlane(t >> 6);
   const int l = t & 63;
   const int lr = l & 31;
-  const int hl = l >> 5;
-  const int KP = KPC ? KPC : a.KP;
+  const int KS = (KPC ? KPC : a.KP) >> 4;
   if (t < kStripRows) nrow[t] = a.nrm[r0 + t];
   const float ncol = a.nrm[c0 + 32 * q + lr];
 
+  constexpr int PARTS = SPLIT ? 2 : 1;
+  constexpr int KA = kStripFrags / PARTS / 4 * 4;  // k-steps per pass
+  constexpr int CH = SPLIT && KPC == 0 ? 2 : 4;      // k-steps loaded together (64 VGPRs)
+  static_assert(KA >= CH, "a pass holds a chunk");
+  const int64_t ra = (r0 >> 5) * KS;
+  const int64_t rb = ((c0 >> 5) + q) * KS;
+  const uint16_t *__restrict__ Bh = a.Xb + rb * kFragElems + l * 8;
+  const uint16_t *__restrict__ Bl = SPLIT ? a.Xlo + rb * kFragElems + l * 8 : nullptr;
   f32x16 acc;
 #pragma unroll
   for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
-  // features per pass: 64, or 32 high + 32 low parts
-  constexpr int kFpp = SPLIT ? 32 : 64;
-  constexpr int kMaxLoads = (kStripOpRows * kStripOpBytes / 16 + kStripWaves * 64 - 1) / (kStripWaves * 64);
-  for (int k0 = 0; k0 < KP; k0 += kFpp) {
-    const int nf = KP - k0 < kFpp ? KP - k0 : kFpp;  // a multiple of 16
-    if constexpr (KPC != 0 && KPC % kFpp == 0) {
-      // every pass full (8 chunks per staged row): one wave instruction
-      // fills 8 staged rows, 1 KB of LDS, straight from global memory
-      // (gfx950 global-to-LDS loads, no register round trip); lane l fills
-      // slot l % 8 of row 8 b + l / 8 with the chunk the swizzle puts there
-      const int lrow = l >> 3, slot = l & 7;
-      for (int b = q; b < kStripOpRows / 8; b += kStripWaves) {
-        const int row = 8 * b + lrow;
-        const int cl = slot ^ ((row >> 1) & 7);
-        const int part = SPLIT ? (cl >> 2) : 0;
-        const int c = SPLIT ? (cl & 3) : cl;
-        const int64_t g = row < kStripRows ? r0 + row : c0 + (row - kStripRows);
-        const uint16_t *src = (SPLIT && part) ? a.Xlo : a.Xb;
-        __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void *)(src + g * KP + k0 + 8 * c),
-            (__attribute__((address_space(3))) void *)(ops + b * 1024), 16, 0, 0);
-      }
-      __builtin_amdgcn_s_waitcnt(0);  // the wave's staged rows have landed
-    } else {
-      const int cpr = nf >> 3;  // chunks per row and part
-      const int per_part = kStripOpRows * cpr;
-      const int total = per_part * (SPLIT ? 2 : 1);
-      u4 v[kMaxLoads];
+  bf16x8 bh[CH], bl[CH];
+  auto load_chunk = [&](int ks, int n) {
 #pragma unroll
-      for (int m = 0; m < kMaxLoads; ++m) {
-        const int e = t + kStripWaves * 64 * m;
-        if (e < total) {
-          const int part = SPLIT ? (e >= per_part) : 0;
-          const int e2 = e - part * per_part;
-          const int row = e2 / cpr, c = e2 - row * cpr;
-          const int64_t g = row < kStripRows ? r0 + row : c0 + (row - kStripRows);
-          const uint16_t *src = (SPLIT && part) ? a.Xlo : a.Xb;
-          v[m] = *reinterpret_cast<const u4 *>(src + g * KP + k0 + 8 * c);
-        }
+    for (int u = 0; u < CH; ++u)
+      if (u < n) {
+        bh[u] = *reinterpret_cast<const bf16x8 *>(Bh + (int64_t)(ks + u) * kFragElems);
+        if constexpr (SPLIT) bl[u] = *reinterpret_cast<const bf16x8 *>(Bl + (int64_t)(ks + u) * kFragElems);
       }
-#pragma unroll
-      for (int m = 0; m < kMaxLoads; ++m) {
-        const int e = t + kStripWaves * 64 * m;
-        if (e < total) {
-          const int part = SPLIT ? (e >= per_part) : 0;
-          const int e2 = e - part * per_part;
-          const int row = e2 / cpr, c = e2 - row * cpr;
-          *reinterpret_cast<u4 *>(ops + strip_chunk(row, c + 4 * part)) = v[m];
-        }
-      }
+  };
+  for (int k0 = 0; k0 < KS; k0 += KA) {
+    const int na = KS - k0 < KA ? KS - k0 : KA;
+    if (k0 > 0) __syncthreads();  // the previous pass is read
+    for (int f = q; f < na * PARTS; f += kStripWaves) {
+      const int part = f >= na ? 1 : 0;
+      load_fragment((SPLIT && part ? a.Xlo : a.Xb) + (ra + k0 + f - part * na) * kFragElems, ops + f * 1024);
     }
+    load_chunk(k0, na);
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the wave's fragments have landed
     __syncthreads();
-    // k-steps of 16 features: lane (lr, hl) reads chunk 2 ks + hl of its
-    // row (split: the low parts are chunks 4 + 2 ks + hl)
-    const int ra = lr, rb = kStripRows + 32 * q + lr;
-    for (int ks = 0; ks < (nf >> 4); ++ks) {
-      const bf16x8 av = *reinterpret_cast<const bf16x8 *>(ops + strip_chunk(ra, 2 * ks + hl));
-      const bf16x8 bv = *reinterpret_cast<const bf16x8 *>(ops + strip_chunk(rb, 2 * ks + hl));
-      if constexpr (SPLIT) {
-        const bf16x8 al = *reinterpret_cast<const bf16x8 *>(ops + strip_chunk(ra, 4 + 2 * ks + hl));
-        const bf16x8 bl = *reinterpret_cast<const bf16x8 *>(ops + strip_chunk(rb, 4 + 2 * ks + hl));
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, bv, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bl, acc, 0, 0, 0);
-      }
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc, 0, 0, 0);
+    for (int ks = 0; ks < na; ks += CH) {
+      const int n = na - ks < CH ? na - ks : CH;
+      if (ks > 0) load_chunk(k0 + ks, n);
+#pragma unroll
+      for (int u = 0; u < CH; ++u)
+        if (u < n) {
+          const bf16x8 av = lds_fragment(ops, ks + u);
+          bf16x8 al = av;
+          if constexpr (SPLIT) al = lds_fragment(ops, na + ks + u);
+          acc = gram_step<SPLIT>(acc, av, al, bh[u], SPLIT ? bl[u] : bh[u]);
+        }
     }
-    __syncthreads();  // the operands are read: the next pass or the output may overwrite them
   }
+  __syncthreads();  // the operands are read: the output may overwrite them
 
   // epilogue: the wave's 32 x 32 block into the staged output; pairs below
   // the threshold are marked and recomputed afterwards (rare: the diagonal,
@@ -602,27 +542,6 @@ __global__ __launch_bounds__(kStripWaves * 64) void gram_strip_kernel(GramArgs a
 // ---------------------------------------------------------------------------
 
 template <bool SPLIT, bool COUNT>
-static void launch_gram_tiles(int KP, dim3 grid, hipStream_t stream, const GramArgs &a, uint32_t l0) {
-  const dim3 block(512);
-  switch (KP) {
-    case 16:
-      hipLaunchKernelGGL((gram_tile_kernel<SPLIT, 16, COUNT>), grid, block, 0, stream, a, l0, grid.x);
-      break;
-    case 32:
-      hipLaunchKernelGGL((gram_tile_kernel<SPLIT, 32, COUNT>), grid, block, 0, stream, a, l0, grid.x);
-      break;
-    case 64:
-      hipLaunchKernelGGL((gram_tile_kernel<SPLIT, 64, COUNT>), grid, block, 0, stream, a, l0, grid.x);
-      break;
-    case 128:
-      hipLaunchKernelGGL((gram_tile_kernel<SPLIT, 128, COUNT>), grid, block, 0, stream, a, l0, grid.x);
-      break;
-    default:
-      hipLaunchKernelGGL((gram_tile_kernel<SPLIT, 0, COUNT>), grid, block, 0, stream, a, l0, grid.x);
-  }
-}
-
-template <bool SPLIT, bool COUNT>
 static void launch_gram_strips(int KP, dim3 grid, hipStream_t stream, const GramArgs &a, uint32_t w0) {
   const dim3 block(kStripWaves * 64);
   switch (KP) {
@@ -676,9 +595,13 @@ static hipError_t launch_gram_t(const float *X, int64_t N, int d, int64_t ldx, f
   float *nrm = reinterpret_cast<float *>(reinterpret_cast<char *>(ws) +
                                          (size_t)Npad * KP * 2 * (split ? 2 : 1));
   const int cpp = KP / 8;
-  const int64_t ppb = cpp <= 256 ? 256 / cpp : 1;
-  hipLaunchKernelGGL(gram_prologue_kernel, dim3((uint32_t)((Npad + ppb - 1) / ppb)), dim3(256), 0, stream,
-                     X, N, d, ldx, Xb, Xlo, nrm, Npad, KP);
+  const size_t lds = (size_t)(cpp < 256 ? cpp : 256) * 32 * sizeof(float);
+  const bool vec = ldx % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+  const dim3 pgrid((uint32_t)(Npad / 32));
+  if (vec)
+    hipLaunchKernelGGL(gram_prologue_kernel<true>, pgrid, dim3(256), lds, stream, X, N, d, ldx, Xb, Xlo, nrm, KP);
+  else
+    hipLaunchKernelGGL(gram_prologue_kernel<false>, pgrid, dim3(256), lds, stream, X, N, d, ldx, Xb, Xlo, nrm, KP);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   GramArgs a{X, N, d, ldx, Xb, Xlo, nrm, KP, D, count};
@@ -707,9 +630,11 @@ static hipError_t launch_gram_t(const float *X, int64_t N, int d, int64_t ldx, f
   for (uint64_t l0 = lo; l0 < hi; l0 += max_blocks) {
     const uint64_t c = hi - l0 < max_blocks ? hi - l0 : max_blocks;
     if (split)
-      launch_gram_tiles<true, COUNT>(KP, dim3((uint32_t)c), stream, a, (uint32_t)l0);
+      hipLaunchKernelGGL((gram_block_kernel<true, COUNT>), dim3((uint32_t)c), dim3(512), 0, stream, a,
+                         (uint32_t)l0, (uint32_t)c);
     else
-      launch_gram_tiles<false, COUNT>(KP, dim3((uint32_t)c), stream, a, (uint32_t)l0);
+      hipLaunchKernelGGL((gram_block_kernel<false, COUNT>), dim3((uint32_t)c), dim3(512), 0, stream, a,
+                         (uint32_t)l0, (uint32_t)c);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   return hipSuccess;

@@ -1,0 +1,39 @@
+"""Gram-form EDM at feature counts where the kernels' loops end or wrap: one
+pass of staged row fragments holds 512 features (split: 256), a block stage
+two k-steps of 16 (split: one), a prologue thread converts chunks of 8
+features and the norms fold chunk sums beyond 256 chunks.  Both kernels agree
+bit for bit, for points that allow 16-byte loads and for points that do not,
+and every pair is within the oracle's stated bound."""
+import numpy as np
+import pytest
+
+from oracle import edm as oedm
+from paper_1308_1419_amd import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+from paper_1308_1419_amd import tdmap  # noqa: E402
+
+
+@pytest.mark.parametrize("prec", ["bf16_gram", "bf16x3_gram"])
+@pytest.mark.parametrize("N,d", [(130, 47), (260, 255), (130, 256), (130, 257), (300, 272), (97, 512),
+                                 (130, 513), (40, 2048), (40, 2056)])
+def test_gram_wide_features(N, d, prec):
+    assert torch.cuda.is_available()
+    X, _ = synth.gaussian_with_near_duplicates(N, d, seed=70 + N + d, frac=0.0)
+    P = torch.empty((N, d + 5), dtype=torch.float32, device="cuda")
+    P[:, 1:d + 1] = torch.from_numpy(X)
+    Xs = [torch.from_numpy(X).cuda(), P[:, 1:d + 1]]  # aligned rows when d % 4 == 0; never
+    outs = [tdmap.edm(x, layout="packed", rho=rho, precision=prec) for x in Xs for rho in (128, 256)]
+    torch.cuda.synchronize()
+    for o in outs[1:]:
+        assert torch.equal(o.view(torch.int32), outs[0].view(torch.int32))
+    got = outs[0].cpu().numpy().astype(np.float64)
+    ref = oedm.edm64_packed(X)
+    i, j = np.tril_indices(N)
+    n = np.linalg.norm(X.astype(np.float64), axis=1)
+    bound = oedm.gram_bound(n[i], n[j], ref, d, split=prec == "bf16x3_gram")
+    err = np.abs(got - ref)
+    assert np.all(got[i == j] == 0.0)
+    assert np.all((err <= bound) | (err <= oedm.fp32_rel_tol() * ref))
