@@ -129,16 +129,17 @@ int tdmap_map_blocks_nodiag(uint64_t lambda0, uint64_t count, uint32_t *ij, void
  *                          thread and row); LTM tiles are taken by g(lambda)
  *                          with every XCD owning one contiguous range of
  *                          lambda;
- *              256       : (LTM, BB) 256 x 256 tiles, each written by 32
- *                          work-groups of 8 rows (strips).  LTM: the tile
- *                          row comes from g(lambda) on the strip index
- *                          divided by 32, and the strips of a tile row are
- *                          taken strip by strip across the row.  Full
- *                          layout: four consecutive cells per thread and
- *                          row, 16-byte stores (D 16-byte aligned and ldd a
- *                          multiple of 4, else the 256-cell tile of the
- *                          rho = 64 / 128 form); packed layouts: four cells
- *                          64 apart per thread and row;
+ *              256       : (LTM, BB) strips of 2 to 8 rows of W x W tiles,
+ *                          2048 cells per 256-thread work-group; W = 1024
+ *                          (512 for d = 4) where D is 16-byte aligned and
+ *                          ldd a multiple of 4 (full layout), 256 in any
+ *                          other full layout, 512 in the packed layouts.
+ *                          LTM: the tile row comes from g(lambda) on the
+ *                          strip index divided by the strips per tile, and
+ *                          the strips of a tile row are taken strip by strip
+ *                          across the row.  Aligned full layout: four
+ *                          consecutive cells per thread and row, 16-byte
+ *                          stores; else four cells 64 apart;
  *              0         : (LTM, BB) chosen by the autotuner among the
  *                          tiles (and, for LTM with a packed layout and an
  *                          aligned D, the sweep rho = 1), timed on the

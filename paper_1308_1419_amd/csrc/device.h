@@ -50,7 +50,8 @@ __device__ __forceinline__ void g_lambda_uniform(uint32_t lam, uint32_t &i, uint
   const float x = __builtin_fmaf(2.0f, (float)lam, 0.25f);
   const float s = x * __builtin_amdgcn_rsqf(x);
   int32_t r = (int32_t)__builtin_amdgcn_readfirstlane((uint32_t)__builtin_fmaxf(s - 0.5f, 0.0f));
-  int32_t c = (int32_t)(lam - (uint32_t)tri64((uint32_t)r));
+  // T(r) mod 2^32 = ((r + 1) / 2) (r | 1)
+  int32_t c = (int32_t)(lam - (((uint32_t)r + 1) >> 1) * ((uint32_t)r | 1));
   if (c < 0) {
     c += r;  // T(r - 1) = T(r) - r
     --r;

@@ -20,9 +20,8 @@
 // the diagonal (Sec. III-B), with the same tile body, which makes the two
 // directly comparable.
 //
-// TS = 256: edm_band_kernel below, which writes each tile as 8-row strips
-// (one strip per work-group, no LDS, row points through the scalar cache);
-// the full layout needs a 16-byte aligned output (else edm_tile_kernel).
+// TS = 256: edm_band_kernel below, which writes low, wide strips (no LDS, row
+// points through the scalar cache).
 // TS = 64 / 128: edm_tile_kernel.
 #include "device.h"
 #include "kernels.h"
@@ -126,66 +125,68 @@ __global__ __launch_bounds__(256) void edm_tile_kernel(EdmArgs a, uint32_t lam0)
   }
 }
 
-// 256 x 256 tiles written as strips.  Tile row I (256 rows) is
-// cut into kBandStrips strips of kBandRows rows, and a work-group writes one
-// strip of one tile, kBandRows x 256 cells.  LTM: work-group w takes tile
-// row I from g(w / kBandStrips) (the paper's block map at the tile level);
-// the kBandStrips (I + 1) work-groups of tile row I are then numbered
-// u = k (I + 1) + J, strip k outer and tile column J inner, so the
-// work-groups in flight finish a few whole rows of the triangle before they
-// move down instead of spreading over the many rows of whole tiles (the
-// write stream stays within a compact window of addresses; measured 15 %
-// faster than whole-tile work-groups at N = 30000).  BB: a kBandStrips n x n
-// grid, blockIdx.y = I, blockIdx.x = k n + J, returning at once for J > I.
-// A wave owns rows w and w + 4 of the strip, so the row point is uniform
-// (read through the scalar cache); there is no LDS and no barrier.  Full
-// layout: a lane owns four consecutive columns and each non-temporal
-// 16-byte store writes a 1 KB row segment.  Packed layouts (rows start at
-// any offset): a lane owns columns l, l + 64, l + 128, l + 192 and each
-// plain 4-byte store instruction writes 256 contiguous bytes; the lines
-// shared by the segments of tiles J and J + 1 meet in L2, those two
-// work-groups being neighbours in w and so on one XCD.  Measured at
-// N = 30000: 323 us full (16-byte and 4-byte stores alike), 292 us packed
-// (16-byte stores of realigned chunks: 414 us).
-constexpr int kBandRows = 8;
+// rho = 256: rows written as strips.  W x W tiles are placed by g(lambda),
+// tile row I is cut into S = W / H strips of H rows, and a 256-thread
+// work-group writes one strip of one tile, H x W = 2048 cells: each wave two
+// rows x 256 columns.  LTM: work-group w takes tile row I from g(w / S) (the
+// paper's block map at the tile level); the S (I + 1) work-groups of tile
+// row I are then numbered u = k (I + 1) + J, strip k outer and tile column J
+// inner, so the work-groups in flight finish a few whole rows of the triangle
+// before they move down instead of spreading over the many rows of whole
+// tiles.  BB: an S n x n grid, blockIdx.y = I, blockIdx.x = k n + J,
+// returning at once for J > I.
+//
+// VEC (full layout, D 16-byte aligned, ldd a multiple of 4): a lane owns
+// four consecutive columns and each non-temporal 16-byte store writes a 1 KB
+// row segment.  Otherwise rows start at any 4-byte boundary: a lane owns
+// columns l, l + 64, l + 128, l + 192, each plain 4-byte store instruction
+// writes 256 contiguous bytes, and the lines shared by neighbouring segments
+// meet in L2 (neighbours in w are on one XCD); non-temporal stores would
+// reach memory as partial lines (store-only, full layout: 395 against
+// 345 us).  The row points are wave-uniform (scalar loads), and there is no
+// LDS traffic and no barrier.
+//
+// What bounds it is the write stream, whose rate falls with the bytes that
+// are being written at a time.  Store-only copies of the launch on the 30000
+// points' triangle (1.8 GB): 325, 309, 292 and 319 us for one row of 1024
+// columns per work-group at 8, 6, 5 and 4 work-groups per CU (full layout);
+// a linear fill of as many bytes as the cells takes 253 to 270 us.  Hence the
+// wide, low strips, and hence fewer work-groups per CU than would fit, by
+// dynamic LDS that no thread uses, once the output is larger than the caches
+// take (kBandSmall).  One row per wave loses more to the loads of its column
+// points, which then serve four cells per lane, than it gains: 342 (full)
+// and 360 us (packed) against 292 and 271.
+// Measured at N = 30000 (us; before: 256-column strips of 8 rows at full
+// residency, and 256-cell tiles for an unaligned full layout), d = 1, 2, 3, 4:
+//   full                312 311 292 291   before 326 330 328 331
+//   full, ldd odd       350   - 350 353   before 828 829 837 844
+//   packed              272 271 271 272   before 286 288 278 292
+template <int LAYOUT, bool VEC, int D>
+struct BandShape {
+  // The strip is widest where rows are written end to end; packed rows are
+  // adjacent, and unaligned full rows gain nothing from width.  At d = 4 the
+  // column points of 1024 columns cost more than the width gives.
+  static constexpr int W = VEC ? (D == 4 ? 512 : 1024) : (LAYOUT == kLayoutFull ? 256 : 512);
+  static constexpr int kAcross = W / 256;     // waves across a strip
+  static constexpr int kDown = 4 / kAcross;   // rows written at a time
+  static constexpr int kRows = 2;             // rows per wave
+  static constexpr int H = kDown * kRows;
+  static constexpr int S = W / H;
+  // work-groups per CU for a large output: fewer where a work-group's loads
+  // (D floats per column) are over sooner
+  static constexpr int kPerCu = VEC ? (D == 4 ? 6 : 4) : (LAYOUT == kLayoutFull ? 8 : (D <= 2 ? 6 : 7));
+  // 160 KB of LDS in 2 KB steps, kPerCu to 8 work-groups of it
+  static constexpr int kIdleLds = kPerCu == 8 ? 0 : (160 / kPerCu / 2 * 2 - 1) * 1024;
+};
+constexpr uint64_t kBandSmall = (uint64_t)64 << 20;  // output bytes
 
-// The four column points of lane l.  XV: X is dense (ldx = D) and 16-byte
-// aligned, so the 4 D floats of columns c .. c + 3 are D aligned 16-byte
-// chunks.
-template <int D, bool XV>
-__device__ __forceinline__ void band_columns(const float *__restrict__ X, int64_t N, int64_t ldx,
-                                             int64_t c, float (&xj)[4][D]) {
-  if constexpr (XV) {
-    if (c + 3 < N) {
-      const f4 *q = reinterpret_cast<const f4 *>(X + c * D);
-      float v[4 * D];
-#pragma unroll
-      for (int m = 0; m < D; ++m) {
-        const f4 t = q[m];
-        v[4 * m] = t.x;
-        v[4 * m + 1] = t.y;
-        v[4 * m + 2] = t.z;
-        v[4 * m + 3] = t.w;
-      }
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int k = 0; k < D; ++k) xj[u][k] = v[u * D + k];
-      return;
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < 4; ++u)
-#pragma unroll
-    for (int k = 0; k < D; ++k) xj[u][k] = c + u < N ? X[(c + u) * ldx + k] : 0.0f;
-}
-
-template <int D, int LAYOUT, bool BB, bool XV>
-__global__ __launch_bounds__(256) void edm_band_kernel(const float *__restrict__ X, int64_t N,
-                                                       int64_t ldx, float *__restrict__ out,
+template <int D, int LAYOUT, bool VEC, bool BB, bool DENSE>
+__global__ __launch_bounds__(256) void edm_band_kernel(const float *__restrict__ X, uint32_t N,
+                                                       int64_t ldx_, float *__restrict__ out,
                                                        int64_t ldd, uint32_t w0) {
-  constexpr int H = kBandRows;
-  constexpr int kBandStrips = 256 / H;
+  using B = BandShape<LAYOUT, VEC, D>;
+  constexpr uint32_t S = B::S;
+  const int64_t ldx = DENSE ? D : ldx_;
   uint32_t I, J, k;
   if constexpr (BB) {
     I = blockIdx.y;
@@ -195,117 +196,124 @@ __global__ __launch_bounds__(256) void edm_band_kernel(const float *__restrict__
   } else {
     const uint32_t w = w0 + xcd_contiguous(blockIdx.x, gridDim.x);
     uint32_t Jt;
-    g_lambda(w / kBandStrips, I, Jt);
-    // w - kBandStrips T(I): Jt = w / kBandStrips - T(I)
-    const uint32_t u = kBandStrips * Jt + w % kBandStrips;
-    k = u / (I + 1);
-    J = u - k * (I + 1);
+    g_lambda_uniform(w / S, I, Jt);
+    const uint32_t u = S * Jt + w % S;
+    // k = u / (I + 1) < S: the single-precision quotient is off by at most
+    // one (u < 2^24), repaired on the scalar unit
+    k = __builtin_amdgcn_readfirstlane((uint32_t)((float)u * __builtin_amdgcn_rcpf((float)(I + 1))));
+    int32_t r = (int32_t)(u - k * (I + 1));
+    if (r < 0) {
+      --k;
+      r += (int32_t)I + 1;
+    } else if (r > (int32_t)I) {
+      ++k;
+      r -= (int32_t)I + 1;
+    }
+    J = (uint32_t)r;
   }
-  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int64_t row0 = (int64_t)I * 256 + (int64_t)k * H;
-  const int64_t c = (int64_t)J * 256 + (threadIdx.x & 63) * 4;
-  const bool interior = J < I && row0 + H <= N;
-  if constexpr (LAYOUT != kLayoutFull) {
-    // packed rows start anywhere: lane l owns columns col0 + l + 64 q and a
-    // store instruction writes 256 contiguous bytes (plain stores)
-    if (interior) {
-      const int64_t cb = (int64_t)J * 256 + (threadIdx.x & 63);
-      float xq[4][D];
+  const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint32_t l = threadIdx.x & 63;
+  // the wave's first row and first column
+  const uint32_t row0 = I * B::W + k * B::H + wv / B::kAcross;
+  const uint32_t c = J * B::W + wv % B::kAcross * 256;
+  const float *__restrict__ Xc = X + (uint64_t)c * (uint64_t)ldx;
+  // the lane's columns, relative to c
+  auto col = [&](int q) -> uint32_t { return VEC ? 4 * l + q : l + 64 * q; };
+  auto load = [&](uint32_t j, float (&x)[D]) {
+#pragma unroll
+    for (int m = 0; m < D; ++m) x[m] = DENSE ? Xc[j * D + m] : Xc[(uint64_t)j * (uint64_t)ldx + m];
+  };
+  float xj[4][D];
+  if (J < I && row0 + (B::kRows - 1) * B::kDown < N) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) load(col(q), xj[q]);
+#pragma unroll
+    for (int r = 0; r < B::kRows; ++r) {
+      const uint32_t i = row0 + B::kDown * r;
+      const float *__restrict__ Xi = X + (uint64_t)i * (uint64_t)ldx;
+      float xi[D];
+#pragma unroll
+      for (int m = 0; m < D; ++m) xi[m] = Xi[m];
+      float *__restrict__ o = out + out_index<LAYOUT>((uint64_t)i, (uint64_t)c, ldd);
+      if constexpr (VEC) {
+        f4 v;
+        v.x = pair_dist<D>(xi, xj[0]);
+        v.y = pair_dist<D>(xi, xj[1]);
+        v.z = pair_dist<D>(xi, xj[2]);
+        v.w = pair_dist<D>(xi, xj[3]);
+        __builtin_nontemporal_store(v, reinterpret_cast<f4 *>(o + 4 * l));
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[l + 64 * q] = pair_dist<D>(xi, xj[q]);
+      }
+    }
+    return;
+  }
+  // diagonal or edge strip: rows below N, cells of the triangle (columns
+  // past the last point are read as the last point, and not written)
+  if (c >= N) return;
+  const uint32_t room = N - 1 - c;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) load(col(q) < room ? col(q) : room, xj[q]);
+#pragma unroll
+  for (int r = 0; r < B::kRows; ++r) {
+    const uint32_t i = row0 + B::kDown * r;
+    if (i >= N || c > i) continue;
+    const float *__restrict__ Xi = X + (uint64_t)i * (uint64_t)ldx;
+    float xi[D], v[4];
+#pragma unroll
+    for (int m = 0; m < D; ++m) xi[m] = Xi[m];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) v[q] = pair_dist<D>(xi, xj[q]);
+    float *__restrict__ o = out + out_index<LAYOUT>((uint64_t)i, (uint64_t)c, ldd);
+    if (VEC && in_triangle<LAYOUT>(i, c + 4 * l + 3)) {
+      const f4 v4 = {v[0], v[1], v[2], v[3]};
+      __builtin_nontemporal_store(v4, reinterpret_cast<f4 *>(o + 4 * l));
+    } else {
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int m = 0; m < D; ++m) xq[q][m] = X[(cb + 64 * q) * ldx + m];
-#pragma unroll
-      for (int r = 0; r < H / 4; ++r) {
-        const int64_t i = row0 + wv + 4 * r;
-        float xi[D];
-#pragma unroll
-        for (int m = 0; m < D; ++m) xi[m] = X[i * ldx + m];
-        float *o = out + out_index<LAYOUT>((uint64_t)i, (uint64_t)cb, 0);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) put<LAYOUT>(pair_dist<D>(xi, xq[q]), o + 64 * q);
-      }
-      return;
-    }
-  }
-  float xj[4][D];
-  band_columns<D, XV>(X, N, ldx, c, xj);
-  if (LAYOUT == kLayoutFull && interior) {
-#pragma unroll
-    for (int r = 0; r < H / 4; ++r) {
-      const int64_t i = row0 + wv + 4 * r;
-      float xi[D];
-#pragma unroll
-      for (int m = 0; m < D; ++m) xi[m] = X[i * ldx + m];
-      f4 v;
-      v.x = pair_dist<D>(xi, xj[0]);
-      v.y = pair_dist<D>(xi, xj[1]);
-      v.z = pair_dist<D>(xi, xj[2]);
-      v.w = pair_dist<D>(xi, xj[3]);
-      __builtin_nontemporal_store(v, reinterpret_cast<f4 *>(out + i * ldd + c));
-    }
-  } else {
-    // diagonal or edge strip: rows below N, cells with j <= i
-#pragma unroll
-    for (int r = 0; r < H / 4; ++r) {
-      const int64_t i = row0 + wv + 4 * r;
-      if (i >= N) break;
-      float xi[D];
-#pragma unroll
-      for (int m = 0; m < D; ++m) xi[m] = X[i * ldx + m];
-      float v[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) v[q] = pair_dist<D>(xi, xj[q]);
-      if constexpr (LAYOUT == kLayoutFull) {
-        float *o = out + i * ldd + c;
-        if (c + 3 <= i) {
-          f4 v4 = {v[0], v[1], v[2], v[3]};
-          __builtin_nontemporal_store(v4, reinterpret_cast<f4 *>(o));
-        } else {
-#pragma unroll
-          for (int q = 0; q < 4; ++q)
-            if (c + q <= i) __builtin_nontemporal_store(v[q], o + q);
-        }
-      } else {
-        const uint64_t idx = out_index<LAYOUT>((uint64_t)i, (uint64_t)c, 0);
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          if (in_triangle<LAYOUT>(i, c + q)) put<LAYOUT>(v[q], out + idx + q);
-      }
+        if (in_triangle<LAYOUT>(i, c + col(q))) o[col(q)] = v[q];
     }
   }
 }
 
-template <int D, int LAYOUT, bool XV>
-static hipError_t launch_band(bool bb, const EdmArgs &a) {
-  constexpr int kBandStrips = 256 / kBandRows;
-  const uint64_t nb = (uint64_t)((a.N + 255) / 256);
+template <int D, int LAYOUT, bool VEC, bool DENSE>
+static hipError_t launch_band_t(bool bb, const EdmArgs &a) {
+  using B = BandShape<LAYOUT, VEC, D>;
+  const uint64_t nb = (uint64_t)((a.N + B::W - 1) / B::W);
+  const uint64_t N = (uint64_t)a.N;
+  const uint32_t lds = N * (N + 1) * 2 >= kBandSmall ? B::kIdleLds : 0;
   if (bb) {
-    hipLaunchKernelGGL((edm_band_kernel<D, LAYOUT, true, XV>), dim3((uint32_t)(kBandStrips * nb), (uint32_t)nb),
-                       dim3(256), 0, a.stream, a.X, a.N, a.ldx, a.D, a.ldd, 0u);
+    hipLaunchKernelGGL((edm_band_kernel<D, LAYOUT, VEC, true, DENSE>),
+                       dim3((uint32_t)(B::S * nb), (uint32_t)nb), dim3(256), lds, a.stream, a.X,
+                       (uint32_t)a.N, a.ldx, a.D, a.ldd, 0u);
     return hipGetLastError();
   }
-  const uint64_t W = (uint64_t)kBandStrips * (nb * (nb + 1) / 2);
+  const uint64_t W = B::S * (nb * (nb + 1) / 2);
   if (W > 0xffffffffull) return hipErrorInvalidValue;  // w is 32-bit (N above 4 million)
   uint64_t lo, hi;
   shard_range(W, a.shard, a.nshards, lo, hi);
   const uint64_t max_blocks = (((uint64_t)1 << 32) - 1) / 256;
   for (uint64_t w0 = lo; w0 < hi; w0 += max_blocks) {
     const uint64_t c = hi - w0 < max_blocks ? hi - w0 : max_blocks;
-    hipLaunchKernelGGL((edm_band_kernel<D, LAYOUT, false, XV>), dim3((uint32_t)c), dim3(256), 0, a.stream,
-                       a.X, a.N, a.ldx, a.D, a.ldd, (uint32_t)w0);
+    hipLaunchKernelGGL((edm_band_kernel<D, LAYOUT, VEC, false, DENSE>), dim3((uint32_t)c), dim3(256), lds,
+                       a.stream, a.X, (uint32_t)a.N, a.ldx, a.D, a.ldd, (uint32_t)w0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
 
+template <int D, int LAYOUT, bool VEC>
+static hipError_t launch_band(bool bb, const EdmArgs &a) {
+  return a.ldx == D ? launch_band_t<D, LAYOUT, VEC, true>(bb, a)
+                    : launch_band_t<D, LAYOUT, VEC, false>(bb, a);
+}
+
 template <int TS, int D, int LAYOUT, bool VEC>
 static hipError_t launch_tiled_t(bool bb, const EdmArgs &a) {
-  if constexpr (TS == 256 && LAYOUT == kLayoutFull && VEC) {
-    // strips of 256-column tiles for the aligned full layout
-    const bool xv = a.ldx == D && (reinterpret_cast<uintptr_t>(a.X) & 15) == 0;
-    return xv ? launch_band<D, kLayoutFull, true>(bb, a) : launch_band<D, kLayoutFull, false>(bb, a);
+  if constexpr (TS == 256) {
+    return launch_band<D, LAYOUT, VEC>(bb, a);
   } else {
     const uint64_t nb = (uint64_t)((a.N + TS - 1) / TS);
     if (bb) {
@@ -328,20 +336,10 @@ static hipError_t launch_tiled_t(bool bb, const EdmArgs &a) {
   }
 }
 
-template <int TS, int D, int LAYOUT>
-static hipError_t launch_tiled_packed(bool bb, const EdmArgs &a) {
-  if constexpr (TS == 256) {
-    const bool xv = a.ldx == D && (reinterpret_cast<uintptr_t>(a.X) & 15) == 0;
-    return xv ? launch_band<D, LAYOUT, true>(bb, a) : launch_band<D, LAYOUT, false>(bb, a);
-  } else {
-    return launch_tiled_t<TS, D, LAYOUT, false>(bb, a);
-  }
-}
-
 template <int TS, int D>
 static hipError_t launch_tiled_d(bool bb, const EdmArgs &a) {
-  if (a.layout == kLayoutPacked) return launch_tiled_packed<TS, D, kLayoutPacked>(bb, a);
-  if (a.layout == kLayoutStrict) return launch_tiled_packed<TS, D, kLayoutStrict>(bb, a);
+  if (a.layout == kLayoutPacked) return launch_tiled_t<TS, D, kLayoutPacked, false>(bb, a);
+  if (a.layout == kLayoutStrict) return launch_tiled_t<TS, D, kLayoutStrict, false>(bb, a);
   const bool aligned = (a.ldd % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.D) & 15) == 0);
   return aligned ? launch_tiled_t<TS, D, kLayoutFull, true>(bb, a)
                  : launch_tiled_t<TS, D, kLayoutFull, false>(bb, a);
