@@ -63,6 +63,23 @@ __device__ __forceinline__ void g_lambda_uniform(uint32_t lam, uint32_t &i, uint
   j = (uint32_t)c;
 }
 
+// q = u / n and the remainder for values that are the same in every lane,
+// u < 2^24 and q + 1 < 2^22: the single-precision quotient is off by at most
+// one, repaired on the scalar unit.
+__device__ __forceinline__ uint32_t div_uniform(uint32_t u, uint32_t n, uint32_t &rem) {
+  uint32_t q = __builtin_amdgcn_readfirstlane((uint32_t)((float)u * __builtin_amdgcn_rcpf((float)n)));
+  int32_t r = (int32_t)(u - q * n);
+  if (r < 0) {
+    --q;
+    r += (int32_t)n;
+  } else if (r >= (int32_t)n) {
+    ++q;
+    r -= (int32_t)n;
+  }
+  rem = (uint32_t)r;
+  return q;
+}
+
 // The map without the diagonal (Sec. II-A, Eq. (10)): lambda enumerates the
 // cells j < i row by row, row i starting at S(i) = i(i-1)/2, and
 // i = floor(sqrt(1/4 + 2 lambda) + 1/2), j = lambda - S(i) (the column is

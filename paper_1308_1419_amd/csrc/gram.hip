@@ -24,17 +24,19 @@
 //     compact window of the packed output and small N makes more
 //     work-groups.
 // Measured (us, blocks / strips, prologue included): N = 100000, d = 64
-// 4295 / 4425 (BF16), 5290 / 5174 (split); N = 50000, d = 256 1694 / 1937;
-// N = 30011, d = 200 split 824 / 897; N = 2000, d = 100 19.4 / 12.6.  The
+// 4390 / 3920 (BF16), 5290 / 5050 (split); N = 50000, d = 256 1580 / 1940;
+// N = 30011, d = 200 split 805 / 880; N = 2000, d = 100 16.7 / 12.2.  The
 // autotuner times both.  With row-major operands, staged through LDS in the
 // strips and loaded by every lane on its own in 128 x 128 tiles, the same
-// sizes took, in the faster of the two, 4403, 6647, 2946, 1872 and 15.7 us.
+// sizes took, in the faster of the two, 4400, 6640, 2946, 1860 and 15.3 us.
 //
 // Split mode (precision BF16X3): each point is held as x = hi + lo with
 // hi = bf16(x) and lo = bf16(x - hi) (x - hi is exact in FP32, and hi + lo
 // is exact in FP32), the norms are those of hi + lo, and the dot product is
 // hi.hi' + hi.lo' + lo.hi', three MFMA products into the same FP32
 // accumulator; only lo.lo' (below 2^-16 of |x||y|) is dropped.
+#include <type_traits>
+
 #include "device.h"
 #include "kernels.h"
 
@@ -137,41 +139,128 @@ __global__ __launch_bounds__(256) void gram_prologue_kernel(const float *__restr
 
 // FP32 difference form with eight interleaved partial sums combined as a
 // tree, which keeps the rounding error of the squared distance near
-// (d/8 + 6) units of roundoff.
-__device__ __forceinline__ float exact_dist(const float *__restrict__ X, int64_t ldx, int d, int64_t i,
-                                         int64_t j) {
-  // a point's distance to itself is exactly 0: the diagonal, most of the
-  // recomputed cells, needs no loads
-  if (i == j) return 0.0f;
-  float s[8];
-#pragma unroll
-  for (int u = 0; u < 8; ++u) s[u] = 0.0f;
+// (d/8 + 6) units of roundoff.  Eight consecutive lanes take one pair: lane u
+// of them sums the features u, u + 8, ..., so that a group's loads are 32
+// consecutive bytes of each point, and the tree runs over lane moves; every
+// lane of the group receives the distance.
+__device__ __forceinline__ float exact_dist8(const float *__restrict__ X, int64_t ldx, int d, int64_t i,
+                                             int64_t j) {
+  const int u = threadIdx.x & 7;
   const float *xi = X + i * ldx;
   const float *xj = X + j * ldx;
-  for (int k0 = 0; k0 < d; k0 += 8) {
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      if (k0 + u < d) {
-        const float t = xi[k0 + u] - xj[k0 + u];
-        s[u] = __builtin_fmaf(t, t, s[u]);
-      }
-    }
+  float s = 0.0f;
+#pragma unroll 4
+  for (int k = u; k < d; k += 8) {
+    const float t = xi[k] - xj[k];
+    s = __builtin_fmaf(t, t, s);
   }
-  const float q = ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
-  return __builtin_amdgcn_sqrtf(q);
+  auto move = [](float v, auto ctrl) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v),
+                                                                 decltype(ctrl)::value, 0xF,
+                                                                 0xF, true));
+  };
+  s += move(s, std::integral_constant<int, 0xB1>());   // quad_perm [1,0,3,2]: 0+1, 2+3, ...
+  s += move(s, std::integral_constant<int, 0x4E>());   // quad_perm [2,3,0,1]: (0+1)+(2+3), ...
+  s += move(s, std::integral_constant<int, 0x141>());  // row_half_mirror: the other four
+  return __builtin_amdgcn_sqrtf(s);
 }
 
 // Accumulator v of a 32 x 32 block holds row (v/4)*8 + (l/32)*4 + v%4 of
 // the block and column l % 32.
 __device__ __forceinline__ int acc_row(int v, int l) { return (v >> 2) * 8 + (l >> 5) * 4 + (v & 3); }
 
-// The epilogue value of one pair from its accumulator and the two squared
-// norms: sqrt(G), or -1 for a pair below the threshold (filled in by the
-// exact recompute).
-__device__ __forceinline__ float gram_value(float acc, float ni, float nj) {
+// The epilogue of one pair from its accumulator and the two squared norms:
+// sqrt(G), and the lane's bit of `low` set for a pair to be recomputed (its
+// square root, possibly of a negative G, is replaced then).
+__device__ __forceinline__ float gram_value(float acc, float ni, float nj, uint64_t &low) {
   const float sn = ni + nj;
   const float G = __builtin_fmaf(-2.0f, acc, sn);
-  return G <= kGramTheta * sn ? -1.0f : __builtin_amdgcn_sqrtf(G);
+  low |= __builtin_amdgcn_ballot_w64(G <= kGramTheta * sn);
+  return __builtin_amdgcn_sqrtf(G);
+}
+// Whether it is one of those.
+__device__ __forceinline__ bool gram_close(float acc, float ni, float nj) {
+  const float sn = ni + nj;
+  return __builtin_fmaf(-2.0f, acc, sn) <= kGramTheta * sn;
+}
+
+// Pairs of a wave to be recomputed, as they are found: positions (row * 256 +
+// column) in the wave's part of the staged output.  Recomputed lane by lane a
+// wave waits for a pair's loads once per accumulator in which some lane has
+// one (N = 60000, d = 10 BF16, where one pair in 170 is recomputed: 2540 us;
+// 1425 with the list); the list spreads the pairs over the wave, eight lanes
+// a pair.
+constexpr int kListLen = 128;  // 63 left over and the 64 of one step
+
+// Recomputes the first n pairs of the list (cells of the triangle, j < i):
+// at(pos) is the staged position, i0 and j0 the pair of position 0.
+template <bool COUNT, typename At>
+__device__ __forceinline__ void recompute_pairs(const GramArgs &a, const uint16_t *list, int n, int64_t i0,
+                                                int64_t j0, At at, uint32_t &nrec) {
+  const int l = threadIdx.x & 63;
+  for (int e0 = 0; e0 < n; e0 += 8) {
+    const int e = e0 + (l >> 3);
+    if (e < n) {
+      const int pos = list[e];
+      const float v = exact_dist8(a.X, a.ldx, a.d, i0 + (pos >> 8), j0 + (pos & 255));
+      if ((l & 7) == 0) {
+        if (COUNT) ++nrec;
+        *at(pos) = v;
+      }
+    }
+  }
+}
+
+// Recomputes a wave's close pairs: bit m of a lane's mask is its pair at
+// position pos(m).  A point with itself, most of the recomputed cells, is
+// exactly 0 and needs no loads; a cell outside the triangle is not stored and
+// set to 0 (both only in blocks that touch the diagonal or the last point,
+// `edge`).  The lanes then hand in one pair each per step, as many steps as
+// the fullest lane has pairs.
+template <bool COUNT, int BITS, typename Pos, typename At>
+__device__ __forceinline__ void recompute_close(const GramArgs &a, uint16_t *list, uint32_t mask, bool edge,
+                                                int64_t i0, int64_t j0, Pos pos, At at, uint32_t &nrec) {
+  const int l = threadIdx.x & 63;
+  if (edge) {
+    uint32_t pairs = 0;
+#pragma unroll
+    for (int m = 0; m < BITS; ++m) {
+      const int p = pos(m);
+      const int64_t i = i0 + (p >> 8), j = j0 + (p & 255);
+      pairs |= (uint32_t)(i < a.N && j < i) << m;
+    }
+    uint32_t other = mask & ~pairs;
+    mask &= pairs;
+    while (other != 0) {
+      const int p = pos(__builtin_ctz(other));
+      other &= other - 1;
+      if (COUNT) nrec += i0 + (p >> 8) < a.N && i0 + (p >> 8) == j0 + (p & 255);
+      *at(p) = 0.0f;
+    }
+  }
+  int count = 0;  // list entries, the same in every lane
+  for (;;) {
+    const uint64_t have = __builtin_amdgcn_ballot_w64(mask != 0);
+    if (have == 0) break;
+    if (mask != 0) {
+      list[count + __builtin_amdgcn_mbcnt_hi((uint32_t)(have >> 32),
+                                             __builtin_amdgcn_mbcnt_lo((uint32_t)have, 0))] =
+          (uint16_t)pos(__builtin_ctz(mask));
+      mask &= mask - 1;
+    }
+    count += __builtin_popcountll(have);
+    __builtin_amdgcn_wave_barrier();  // the wave reads its own LDS writes
+    if (count >= 64) {
+      recompute_pairs<COUNT>(a, list, 64, i0, j0, at, nrec);
+      count -= 64;
+      __builtin_amdgcn_wave_barrier();
+      const uint16_t rest = list[64 + l];
+      __builtin_amdgcn_wave_barrier();
+      list[l] = rest;
+      __builtin_amdgcn_wave_barrier();
+    }
+  }
+  recompute_pairs<COUNT>(a, list, count, i0, j0, at, nrec);
 }
 
 // One 1 KB fragment from global memory straight into LDS: lane l's 16 bytes
@@ -217,16 +306,17 @@ static_assert(8 * 32 * 64 * 4 <= 3 * kBlkStage, "the staged output overlays the 
 template <bool SPLIT, bool COUNT>
 __global__ __launch_bounds__(512, 4) void gram_block_kernel(GramArgs a, uint32_t w0, uint32_t nblk) {
   __shared__ __align__(16) unsigned char ops[3 * kBlkStage];
+  __shared__ uint16_t list[8][kListLen];
+  __shared__ float nrow[kBlkRows];
   const uint32_t w = w0 + xcd_contiguous(blockIdx.x, nblk);
-  // tile row I2 of 256 rows holds 2 (I2 + 1) work-groups: the upper 128
-  // rows across all its tiles, then the lower ones
-  uint32_t I2, Jt;
-  g_lambda_uniform(w >> 1, I2, Jt);
-  const uint32_t u = 2 * Jt + (w & 1);
-  const uint32_t half = u > I2 ? 1 : 0;
-  const uint32_t J = u - half * (I2 + 1);
+  // g places 256 x 256 tiles, the two 128-row halves of a tile inner: its
+  // column points then serve 256 rows from L2 (N = 50000, d = 256: 1704 us
+  // against 1741 with the upper halves of a tile row before the lower ones and
+  // 1777 with 512 x 512 squares, four bands inner)
+  uint32_t I2, J;
+  g_lambda_uniform(w >> 1, I2, J);
   const int64_t N = a.N;
-  const int64_t r0 = (int64_t)I2 * 256 + half * kBlkRows;
+  const int64_t r0 = (int64_t)I2 * 256 + (w & 1) * kBlkRows;
   const int64_t c0 = (int64_t)J * 256;
   if (r0 >= N) return;  // uniform
   const int q = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -234,7 +324,13 @@ __global__ __launch_bounds__(512, 4) void gram_block_kernel(GramArgs a, uint32_t
   const int lr = l & 31;
   const int KS = a.KP >> 4;
   const int wr = q >> 2, wc = q & 3;
+  const int64_t cw = c0 + 64 * wc;
   const int stages = SPLIT ? KS : (KS + 1) >> 1;
+  // the norms, loaded ahead of the operands: nothing waits for them later
+  float nc[2];
+#pragma unroll
+  for (int y = 0; y < 2; ++y) nc[y] = a.nrm[cw + 32 * y + lr];
+  if (threadIdx.x < kBlkRows) nrow[threadIdx.x] = a.nrm[r0 + threadIdx.x];
 
   // fragment f of a stage: point block f / 2 (rows first), f odd: the second
   // k-step (absent when KS is odd and the stage the last) or the low part
@@ -305,41 +401,34 @@ __global__ __launch_bounds__(512, 4) void gram_block_kernel(GramArgs a, uint32_t
 
   // output: 32 rows x 64 columns at a time through the wave's own 8 KB of
   // LDS, then whole rows of 64 cells (256 contiguous bytes per store)
-  const int64_t cw = c0 + 64 * wc;
   float *st = reinterpret_cast<float *>(ops) + q * 32 * 64;
-  float nc[2];
-#pragma unroll
-  for (int y = 0; y < 2; ++y) nc[y] = a.nrm[cw + 32 * y + lr];
   uint32_t nrec = 0;
 #pragma unroll
   for (int x = 0; x < 2; ++x) {
     const int64_t rw = r0 + 64 * wr + 32 * x;
     if (rw >= N || cw > rw + 31) continue;  // no cell of the triangle (uniform)
-    uint32_t flag[2] = {0, 0};
+    uint64_t low = 0;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
       const int rr = acc_row(v, l);
-      const float ni = a.nrm[rw + rr];
+      const float ni = nrow[64 * wr + 32 * x + rr];
 #pragma unroll
       for (int y = 0; y < 2; ++y) {
-        const float e = acc[x][y][v];
-        const float g = gram_value(e, ni, nc[y]);
-        flag[y] |= (uint32_t)(g < 0.0f) << v;
-        st[rr * 64 + 32 * y + lr] = g < 0.0f ? 0.0f : g;
+        const float e = acc[x][y][v];  // (copied out: a bit cast of a vector element is avoided)
+        st[rr * 64 + 32 * y + lr] = gram_value(e, ni, nc[y], low);
       }
     }
-    if ((flag[0] | flag[1]) != 0) {
-#pragma unroll 1
+    if (low != 0) {
+      uint32_t mask = 0;
+#pragma unroll
       for (int m = 0; m < 32; ++m) {
-        const int y = m >> 4, v = m & 15;
-        if (((y ? flag[1] : flag[0]) >> v) & 1u) {
-          const int rr = acc_row(v, l);
-          const int64_t i = rw + rr, j = cw + 32 * y + lr;
-          const bool cell = i < N && j <= i;
-          if (COUNT) nrec += cell;
-          st[rr * 64 + 32 * y + lr] = cell ? exact_dist(a.X, a.ldx, a.d, i, j) : 0.0f;
-        }
+        const float e = acc[x][m >> 4][m & 15];
+        mask |= (uint32_t)gram_close(e, nrow[64 * wr + 32 * x + acc_row(m & 15, l)], nc[m >> 4]) << m;
       }
+      recompute_close<COUNT, 32>(
+          a, list[q], mask, cw + 63 >= rw || rw + 32 > N, rw, cw,
+          [&](int m) { return acc_row(m & 15, l) * 256 + 32 * (m >> 4) + lr; },
+          [&](int p) { return st + (p >> 8) * 64 + (p & 255); }, nrec);
     }
     __builtin_amdgcn_wave_barrier();  // the wave reads its own LDS writes
     // row rw + r starts at T(rw) + r rw + r (r + 1) / 2
@@ -362,12 +451,19 @@ __global__ __launch_bounds__(512, 4) void gram_block_kernel(GramArgs a, uint32_t
 // ---------------------------------------------------------------------------
 
 // Tile row I (256 rows) is cut into kStripsPerTile strips of 32 rows and a
-// work-group computes one strip of one tile, 32 x 256 cells.  The strips of
-// tile row I are numbered u = 0 .. 8 (I + 1) - 1 and taken in column groups
-// of kStripGroup tiles: group outer, strip next, tile column inner, so the
-// work-groups in flight write a few 32-row bands of the packed triangle (a
-// compact window of addresses) while a group's BF16 column points stay in
-// L2 across its 8 strips.
+// work-group computes one strip of one tile, 32 x 256 cells.  What bounds it
+// is the write stream (N = 100000, d = 64 BF16, tiles in groups of eight: 4.4
+// ms, without the products 4.0, without the stores 1.45; 3.9 in bands), and
+// with it the order in which the strips of a tile row are taken,
+// u = 0 .. 8 (I + 1) - 1:
+//   - up to 64 features (split: 32): two bands of kStripBand strips, swept
+//     across the tile row with the strip inner, so that a band's rows are
+//     written end to end, and three work-groups per CU for large outputs (the fewer bytes being written at a time, the
+//     better: 4.16 ms with four; at two the loads are no longer hidden, 4.34);
+//   - more: column groups of kStripGroup tiles, group outer, strip next, tile
+//     inner: a group's column points then stay in L2 across its 8 strips,
+//     which the wider operands need more (d = 64 split: 5.05 ms, 5.25 in
+//     bands, 5.4 with three work-groups per CU).
 //
 // Operands: wave q computes the 32 x 32 block of columns [32 q, 32 q + 32)
 // and is the only one to use their fragments, so it loads those straight
@@ -387,26 +483,34 @@ constexpr int kStripPitch = 260;  // floats per staged output row
 constexpr int kStripBytes = kStripRows * kStripPitch * 4;
 constexpr int kStripFrags = kStripBytes / 1024;  // fragments that fit the area
 constexpr uint32_t kStripGroup = 8;
+constexpr uint32_t kStripBand = 4;
+template <bool SPLIT, int KPC>
+constexpr bool kStripBands = KPC != 0 && KPC * (SPLIT ? 2 : 1) <= 64;
+constexpr uint32_t kStripIdleLds = 16 * 1024;               // leaves three work-groups per CU
+constexpr uint64_t kStripSmall = (uint64_t)64 << 20;        // output bytes
 
-__device__ __forceinline__ void strip_order(uint32_t w, uint32_t group, uint32_t &I, uint32_t &k,
-                                            uint32_t &J) {
+template <bool BANDS>
+__device__ __forceinline__ void strip_order(uint32_t w, uint32_t &I, uint32_t &k, uint32_t &J) {
   uint32_t Jt;
-  g_lambda(w / kStripsPerTile, I, Jt);
+  g_lambda_uniform(w / kStripsPerTile, I, Jt);
   // u: this work-group's place among the 8 (I + 1) strips of tile row I
   const uint32_t u = kStripsPerTile * Jt + w % kStripsPerTile;
-  const uint32_t ntile = I + 1;
-  const uint32_t gs = group < ntile ? group : ntile;
-  const uint32_t nfull = ntile / gs;
-  const uint32_t span = gs * kStripsPerTile;
-  if (u < nfull * span) {
-    const uint32_t g = u / span, r = u - g * span;
-    k = r / gs;
-    J = g * gs + (r - k * gs);
-  } else {
-    const uint32_t rem = ntile - nfull * gs;  // the last, narrower group
-    const uint32_t r = u - nfull * span;
-    k = r / rem;
-    J = nfull * gs + (r - k * rem);
+  if constexpr (BANDS) {
+    uint32_t r;
+    const uint32_t b = div_uniform(u, kStripBand * (I + 1), r);
+    J = r / kStripBand;
+    k = b * kStripBand + r % kStripBand;
+    return;
+  }
+  constexpr uint32_t span = kStripGroup * kStripsPerTile;
+  const uint32_t g = u / span, r = u % span;
+  const uint32_t left = I + 1 - g * kStripGroup;  // tiles from this group on
+  if (left >= kStripGroup) {
+    k = r / kStripGroup;
+    J = g * kStripGroup + r % kStripGroup;
+  } else {  // the last, narrower group
+    k = div_uniform(r, left, J);
+    J += g * kStripGroup;
   }
 }
 
@@ -415,10 +519,11 @@ __global__ __launch_bounds__(kStripWaves * 64, 8) void gram_strip_kernel(GramArg
                                                                          uint32_t nblk) {
   __shared__ __align__(16) unsigned char ops[kStripBytes];
   __shared__ float nrow[kStripRows];
+  __shared__ uint16_t list[kStripWaves][kListLen];
   float *st = reinterpret_cast<float *>(ops);  // after the products
   const uint32_t w = w0 + xcd_contiguous(blockIdx.x, nblk);
   uint32_t I, k, J;
-  strip_order(w, kStripGroup, I, k, J);
+  strip_order<kStripBands<SPLIT, KPC>>(w, I, k, J);
   const int64_t N = a.N;
   const int64_t r0 = (int64_t)I * 256 + (int64_t)k * kStripRows;
   if (r0 >= N) return;  // a strip past the last point (uniform)
@@ -477,32 +582,27 @@ __global__ __launch_bounds__(kStripWaves * 64, 8) void gram_strip_kernel(GramArg
   }
   __syncthreads();  // the operands are read: the output may overwrite them
 
-  // epilogue: the wave's 32 x 32 block into the staged output; pairs below
-  // the threshold are marked and recomputed afterwards (rare: the diagonal,
-  // which needs no loads, and near-duplicate pairs)
+  // epilogue: the wave's 32 x 32 block into the staged output
   const int col = 32 * q + lr;
-  uint32_t rflag = 0;
+  uint64_t low = 0;
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
     const int rr = acc_row(v, l);
     const float e = acc[v];  // (copied out: a bit cast of a vector element is avoided)
-    const float g = gram_value(e, nrow[rr], ncol);
-    rflag |= (uint32_t)(g < 0.0f) << v;
-    st[rr * kStripPitch + col] = g < 0.0f ? 0.0f : g;
+    st[rr * kStripPitch + col] = gram_value(e, nrow[rr], ncol, low);
   }
   uint32_t nrec = 0;
-  if (rflag != 0) {
-#pragma unroll 1
+  if (low != 0) {
+    uint32_t mask = 0;
+#pragma unroll
     for (int v = 0; v < 16; ++v) {
-      if ((rflag >> v) & 1u) {
-        const int rr = acc_row(v, l);
-        const int64_t i = r0 + rr;
-        const int64_t j = c0 + col;
-        const bool cell = i < N && j <= i;
-        if (COUNT) nrec += cell;
-        st[rr * kStripPitch + col] = cell ? exact_dist(a.X, a.ldx, a.d, i, j) : 0.0f;
-      }
+      const float e = acc[v];
+      mask |= (uint32_t)gram_close(e, nrow[acc_row(v, l)], ncol) << v;
     }
+    recompute_close<COUNT, 16>(
+        a, list[q], mask, diag || r0 + kStripRows > N, r0, c0 + 32 * q,
+        [&](int v) { return acc_row(v, l) * 256 + lr; },
+        [&](int p) { return st + (p >> 8) * kStripPitch + 32 * q + (p & 255); }, nrec);
   }
   if (COUNT && nrec) atomicAdd(a.rec_count, (unsigned long long)nrec);
   __syncthreads();
@@ -541,24 +641,22 @@ __global__ __launch_bounds__(kStripWaves * 64, 8) void gram_strip_kernel(GramArg
 // host side
 // ---------------------------------------------------------------------------
 
+template <bool SPLIT, int KPC, bool COUNT>
+static void launch_strip_kernel(dim3 grid, hipStream_t stream, const GramArgs &a, uint32_t w0) {
+  const uint64_t N = (uint64_t)a.N;
+  const uint32_t lds = kStripBands<SPLIT, KPC> && N * (N + 1) * 2 >= kStripSmall ? kStripIdleLds : 0;
+  hipLaunchKernelGGL((gram_strip_kernel<SPLIT, KPC, COUNT>), grid, dim3(kStripWaves * 64), lds, stream, a, w0,
+                     grid.x);
+}
+
 template <bool SPLIT, bool COUNT>
 static void launch_gram_strips(int KP, dim3 grid, hipStream_t stream, const GramArgs &a, uint32_t w0) {
-  const dim3 block(kStripWaves * 64);
   switch (KP) {
-    case 16:
-      hipLaunchKernelGGL((gram_strip_kernel<SPLIT, 16, COUNT>), grid, block, 0, stream, a, w0, grid.x);
-      break;
-    case 32:
-      hipLaunchKernelGGL((gram_strip_kernel<SPLIT, 32, COUNT>), grid, block, 0, stream, a, w0, grid.x);
-      break;
-    case 64:
-      hipLaunchKernelGGL((gram_strip_kernel<SPLIT, 64, COUNT>), grid, block, 0, stream, a, w0, grid.x);
-      break;
-    case 128:
-      hipLaunchKernelGGL((gram_strip_kernel<SPLIT, 128, COUNT>), grid, block, 0, stream, a, w0, grid.x);
-      break;
-    default:
-      hipLaunchKernelGGL((gram_strip_kernel<SPLIT, 0, COUNT>), grid, block, 0, stream, a, w0, grid.x);
+    case 16: return launch_strip_kernel<SPLIT, 16, COUNT>(grid, stream, a, w0);
+    case 32: return launch_strip_kernel<SPLIT, 32, COUNT>(grid, stream, a, w0);
+    case 64: return launch_strip_kernel<SPLIT, 64, COUNT>(grid, stream, a, w0);
+    case 128: return launch_strip_kernel<SPLIT, 128, COUNT>(grid, stream, a, w0);
+    default: return launch_strip_kernel<SPLIT, 0, COUNT>(grid, stream, a, w0);
   }
 }
 
@@ -570,11 +668,14 @@ size_t gram_workspace_bytes(int64_t N, int d, bool split) {
   return (size_t)Npad * (size_t)KP * 2 * (split ? 2 : 1) + (size_t)Npad * 4;
 }
 
+// Work-groups of the block kernel: two per 256 x 256 tile.
+static uint64_t gram_blocks(int64_t N) {
+  const uint64_t nb = (uint64_t)((N + 255) / 256);
+  return nb * (nb + 1);
+}
+
 bool gram_supported(int64_t N, int ts) {
-  if (ts == 128) {
-    const uint64_t nb2 = (uint64_t)((N + 255) / 256);
-    return nb2 * (nb2 + 1) <= 0xffffffffull;
-  }
+  if (ts == 128) return gram_blocks(N) <= 0xffffffffull;
   if (ts == 256) {
     const uint64_t nb = (uint64_t)((N + 255) / 256);
     return (uint64_t)kStripsPerTile * (nb * (nb + 1) / 2) <= 0xffffffffull;
@@ -622,8 +723,7 @@ static hipError_t launch_gram_t(const float *X, int64_t N, int d, int64_t ldx, f
     return hipSuccess;
   }
   if (ts != 128) return hipErrorInvalidValue;
-  const uint64_t nb2 = (uint64_t)(Npad / 256);
-  const uint64_t T = nb2 * (nb2 + 1);  // two work-groups per 256 x 256 tile
+  const uint64_t T = gram_blocks(N);
   uint64_t lo, hi;
   shard_range(T, shard, nshards, lo, hi);
   const uint64_t max_blocks = (((uint64_t)1 << 32) - 1) / 512;

@@ -197,19 +197,7 @@ __global__ __launch_bounds__(256) void edm_band_kernel(const float *__restrict__
     const uint32_t w = w0 + xcd_contiguous(blockIdx.x, gridDim.x);
     uint32_t Jt;
     g_lambda_uniform(w / S, I, Jt);
-    const uint32_t u = S * Jt + w % S;
-    // k = u / (I + 1) < S: the single-precision quotient is off by at most
-    // one (u < 2^24), repaired on the scalar unit
-    k = __builtin_amdgcn_readfirstlane((uint32_t)((float)u * __builtin_amdgcn_rcpf((float)(I + 1))));
-    int32_t r = (int32_t)(u - k * (I + 1));
-    if (r < 0) {
-      --k;
-      r += (int32_t)I + 1;
-    } else if (r > (int32_t)I) {
-      ++k;
-      r -= (int32_t)I + 1;
-    }
-    J = (uint32_t)r;
+    k = div_uniform(S * Jt + w % S, I + 1, J);
   }
   const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t l = threadIdx.x & 63;

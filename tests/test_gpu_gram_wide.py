@@ -37,3 +37,31 @@ def test_gram_wide_features(N, d, prec):
     err = np.abs(got - ref)
     assert np.all(got[i == j] == 0.0)
     assert np.all((err <= bound) | (err <= oedm.fp32_rel_tol() * ref))
+
+
+@pytest.mark.parametrize("prec", ["bf16_gram", "bf16x3_gram"])
+@pytest.mark.parametrize("N,d,copies", [(40, 3, 40), (257, 16, 257), (300, 24, 70), (300, 5, 129)])
+def test_gram_many_recomputed(N, d, copies, prec):
+    # `copies` points lie within 1e-3 of one another, so up to every pair of a
+    # 32 x 32 block is recomputed: a wave's list of such pairs fills and is
+    # flushed (64 pairs), with rest and without.  All of them meet the FP32
+    # rule of eight interleaved sums, (d / 8 + 6) units of roundoff, doubled
+    # for the sum under the root's relative error and the root itself.
+    assert torch.cuda.is_available()
+    rng = np.random.Generator(np.random.PCG64(N + d))
+    X = rng.standard_normal((N, d), dtype=np.float32)
+    pick = np.sort(rng.permutation(N)[:copies])
+    X[pick] = X[pick[0]] + rng.standard_normal((copies, d), dtype=np.float32) * np.float32(1e-3)
+    Xd = torch.from_numpy(X).cuda()
+    ref = oedm.edm64_packed(X)
+    i, j = np.tril_indices(N)
+    near = np.isin(i, pick) & np.isin(j, pick)
+    outs = [tdmap.gram_recompute_count(Xd, prec, rho=rho) for rho in (128, 256)]
+    torch.cuda.synchronize()
+    (a, ca), (b, cb) = outs
+    assert torch.equal(a.view(torch.int32), b.view(torch.int32)) and int(ca) == int(cb)
+    assert int(ca) >= int(near.sum()) + int((~near & (i == j)).sum())
+    got = a.cpu().numpy().astype(np.float64)
+    assert np.all(got[i == j] == 0.0)
+    err = np.abs(got - ref)[near]
+    assert np.all(err <= 2 * (d / 8 + 6) * 2.0 ** -24 * ref[near])
