@@ -182,43 +182,37 @@ __global__ __launch_bounds__(256) void edm_sweep_kernel(const float *__restrict_
   }
 }
 
-// Batched: the positions [out_off[0], out_off[S]) of the concatenated
-// packed triangles, cut into chunks of kBatchChunk consecutive positions.
-// set_of finds the set holding position e by a galloping search from a set
-// s with out_off[s] <= e; empty sets are skipped.
-__device__ __forceinline__ int32_t set_of(const int64_t *__restrict__ oo, int32_t S, int32_t s,
-                                          uint64_t e) {
-  if ((uint64_t)oo[s + 1] > e) return s;
-  // gallop: find hi with oo[hi] > e
-  int32_t lo = s + 1, step = 1;
-  while (lo + step < S && (uint64_t)oo[lo + step] <= e) {
-    lo += step;
-    step <<= 1;
-  }
-  int32_t hi = lo + step < S ? lo + step : S;  // oo[hi] > e (oo[S] = total > e)
-  // largest t in [lo, hi) with oo[t] <= e
-  while (hi - lo > 1) {
-    const int32_t mid = (lo + hi) >> 1;
-    if ((uint64_t)oo[mid] <= e) lo = mid; else hi = mid;
-  }
-  return lo;
-}
-
-// A persistent grid of kBatchWgsPerCu 1024-thread work-groups per CU.
-// Work-group b of G owns chunks [C b / G, C (b + 1) / G) of the C chunks
-// and walks them in address order: every work-group writes one contiguous
-// stretch of the output, and the grid is balanced to one chunk.  A chunk
-// that lies inside one set of at most kBatchLdsFloats / D points reads the
-// set's points from LDS, staged when the walk enters the set, so its loop
-// issues no global load and its stores never wait (vmcnt counts loads and
-// stores alike, and a wait for a load waits for every store issued before
-// it).  Lane l of wave w writes positions c0 + 1024 w + l + 64 q, q < 16:
-// each 4-byte store instruction covers 256 contiguous bytes.  The chunk at
-// the end of a set, and every chunk of a set too large for LDS, map each
-// position on its own (set search and 64-bit g) and read global memory.
+// Batched: the positions [out_off[0], out_off[S]) of the concatenated packed
+// triangles.  A persistent grid of kBatchWgsPerCu 1024-thread work-groups per
+// CU: work-group b of G owns the units [U b / G, U (b + 1) / G) of kBatchUnit
+// positions, one contiguous stretch of the output, and walks it in chunks
+// whose points it stages in LDS, so that a chunk's stores never wait (vmcnt
+// counts loads and stores alike, and a wait for a load waits for every store
+// issued before it):
+//   - a full chunk inside one set: the set's points, staged once when the walk
+//     enters the set, 16 positions per lane in an unrolled loop;
+//   - anything else (the end of a set, sets smaller than a chunk, the end of
+//     the stretch): up to kBatchMulti positions over as many sets as the table
+//     and the points' LDS hold.  Consecutive sets' points are adjacent in X,
+//     so one pass of loads stages them all; each lane finds the set of its
+//     first position by a search of the table in LDS, follows the table from
+//     there, and maps every position on its own.
+// A set too large for LDS maps each position on its own and reads global
+// memory.  Lane l of wave w writes positions l + 64 q of the wave's stretch of
+// the chunk: each 4-byte store instruction covers 256 contiguous bytes.
+// Measured (us, d = 3): 3000 sets of 0 to 139 points 17.7 (57 when each
+// position outside a full chunk searched its set and read global memory; the
+// 64-cell tiles 40 with their prefix sums); 4096 sets of 8 to 32 points under
+// 10.7, the time to issue the call (107); 500 sets of 250 to 1000 points 101
+// (112); 1024 sets of 64 to 4096 points 1950 (1950), bound by the write rate
+// of a persistent grid.
 constexpr int kBatchThreads = 1024;
 constexpr int kBatchPer = 16;                           // positions per lane per chunk
 constexpr int kBatchChunk = kBatchThreads * kBatchPer;  // 16384 positions
+constexpr int kBatchQuarter = kBatchChunk / 4;
+constexpr int kBatchMulti = 2 * kBatchChunk;
+constexpr int kBatchUnit = kBatchThreads;
+constexpr int kBatchTable = kBatchThreads;              // sets of a chunk
 constexpr int kBatchLdsFloats = 16384;                  // 64 KB
 constexpr int kBatchWgsPerCu = 2;
 
@@ -228,80 +222,245 @@ __device__ __forceinline__ void lds_pt(const float *p, float (&v)[D]) {
   for (int k = 0; k < D; ++k) v[k] = p[k];
 }
 
+// g(lambda) for lambda < 2^28 that differs from lane to lane.
+__device__ __forceinline__ void g_lambda_small(uint32_t lam, uint32_t &i, uint32_t &j) {
+  const float x = __builtin_fmaf(2.0f, (float)lam, 0.25f);
+  const float s = x * __builtin_amdgcn_rsqf(x);
+  int32_t r = (int32_t)__builtin_fmaxf(s - 0.5f, 0.0f);
+  int32_t c = (int32_t)lam - ((r + 1) >> 1) * (r | 1);  // T(r) = ((r + 1) / 2) (r | 1)
+  if (c < 0) {
+    c += r;
+    --r;
+  } else if (c > r) {
+    c -= r + 1;
+    ++r;
+  }
+  i = (uint32_t)r;
+  j = (uint32_t)c;
+}
+
+// PER x 1024 positions inside one set, from its position lam on; xp: the
+// set's points in LDS, o: the position's cell.  The walk keeps the LDS
+// offsets iD = i D and jD = j D (additions only; j > i is jD > iD, and a row
+// of i + 1 cells is (i + 1) D floats).
+template <int D, int PER>
+__device__ __forceinline__ void set_chunk(const float *xp, uint32_t lam, float *__restrict__ o, uint32_t w,
+                                          uint32_t l) {
+  const uint32_t off = w * (64 * PER) + l;
+  uint32_t i, j;
+  g_lambda_small(lam + off, i, j);
+  uint32_t iD = i * D, jD = j * D;
+  float xi[D], xj[D];
+  lds_pt<D>(xp + iD, xi);
+#pragma unroll
+  for (int q = 0; q < PER; ++q) {
+    if (q > 0) {
+      jD += 64 * D;
+      if (jD > iD) {
+        do {
+          iD += D;
+          jD -= iD;
+        } while (jD > iD);
+        lds_pt<D>(xp + iD, xi);
+      }
+    }
+    lds_pt<D>(xp + jD, xj);
+    __builtin_nontemporal_store(pair_dist<D>(xi, xj), o + off + 64 * q);
+  }
+}
+
 template <int D>
 __global__ __launch_bounds__(kBatchThreads, 8) void edm_batched_sweep_kernel(
     const float *__restrict__ X, const int64_t *__restrict__ point_off,
     const int64_t *__restrict__ oo, int32_t S, float *__restrict__ out) {
-  __shared__ float xs[kBatchLdsFloats];
+  __shared__ __align__(16) float xs[kBatchLdsFloats];
+  // table of a chunk: first position of each set (relative to the chunk's
+  // first; one more entry ends the last) and its points' place in xs
+  __shared__ int32_t tab_o[kBatchTable + 1];
+  __shared__ int32_t tab_p[kBatchTable];
   const uint64_t first = (uint64_t)oo[0];
   const uint64_t total = (uint64_t)oo[S];
-  const uint64_t chunks = (total - first + kBatchChunk - 1) / kBatchChunk;
+  const uint64_t units = (total - first + kBatchUnit - 1) / kBatchUnit;
   const uint64_t G = gridDim.x;
-  const uint64_t c_end = chunks * (blockIdx.x + 1) / G;
+  const uint64_t u0 = units * blockIdx.x / G, u1 = units * (blockIdx.x + 1) / G;
+  if (u0 == u1) return;
+  const uint64_t end = first + u1 * kBatchUnit < total ? first + u1 * kBatchUnit : total;
+  uint64_t e = first + u0 * kBatchUnit;
   const uint32_t t = threadIdx.x;
-  const uint32_t off = (t >> 6) * (64 * kBatchPer) + (t & 63);
-  // the set of the current chunk's first position, its output range and
-  // its points (the same values in every thread)
+  const uint32_t w = __builtin_amdgcn_readfirstlane(t >> 6), l = t & 63;
+
+  // s: the largest set with out_off[s] <= e (so a set with cells), found by
+  // all threads at once, 1024 candidates a round
   int32_t s = 0;
-  uint64_t s_beg = first, s_end = (uint64_t)oo[1];
-  int64_t p0 = point_off[0], n = point_off[1] - point_off[0];
-  int32_t staged = -1;
-  for (uint64_t c = chunks * blockIdx.x / G; c < c_end; ++c) {
-    const uint64_t c0 = first + c * kBatchChunk;
-    if (c0 >= s_end) {
-      s = set_of(oo, S, s, c0);
-      s_beg = (uint64_t)oo[s];
-      s_end = (uint64_t)oo[s + 1];
-      p0 = point_off[s];
-      n = point_off[s + 1] - p0;
-    }
-    if (c0 + kBatchChunk <= s_end && n <= kBatchLdsFloats / D) {
-      if (staged != s) {
-        __syncthreads();  // every wave is done with the previous set
-        const float *__restrict__ Xs = X + p0 * D;
-        for (int e = (int)t; e < (int)n * D; e += kBatchThreads) xs[e] = Xs[e];
-        __syncthreads();
-        staged = s;
-      }
-      // lambda < n(n+1)/2 < 2^28 here: the 32-bit map.  The walk keeps
-      // the LDS offsets iD = i D and jD = j D (additions only; j > i is
-      // jD > iD, and a row of i + 1 cells is (i + 1) D floats).
-      uint32_t i, j;
-      g_lambda((uint32_t)(c0 - s_beg) + off, i, j);
-      uint32_t iD = i * D, jD = j * D;
-      float xi[D], xj[D];
-      lds_pt<D>(xs + iD, xi);
+  for (int32_t n = S; n > 1;) {
+    const int32_t step = (n + kBatchThreads - 1) / kBatchThreads;
+    const int64_t k = (int64_t)t * step;
+    const int32_t at = __syncthreads_count(k < n && (uint64_t)oo[s + k] <= e) - 1;
+    s += at * step;
+    n = n - at * step < step ? n - at * step : step;
+  }
+  // xs holds the points [have0, have1)
+  int64_t have0 = 0, have1 = 0;
+  // makes it hold [q0, q1), keeping what is there if both fit; the caller has
+  // passed a barrier since the last use of xs and passes one before the next
+  auto stage = [&](int64_t q0, int64_t q1) {
+    if (q0 >= have0 && q1 <= have1) return;
+    int64_t from = have1;
+    if (q0 < have0 || q0 > have1 || q1 - have0 > kBatchLdsFloats / D) have0 = from = q0;
+    // eight loads in flight per thread
+    const float *__restrict__ src = X + from * D;
+    float *dst = xs + (int)(from - have0) * D;
+    const int len = (int)(q1 - from) * D;
+    for (int m0 = (int)t; m0 < len; m0 += 8 * kBatchThreads) {
+      float v[8];
 #pragma unroll
-      for (int q = 0; q < kBatchPer; ++q) {
-        if (q > 0) {
-          jD += 64 * D;
-          if (jD > iD) {
-            do {
-              iD += D;
-              jD -= iD;
-            } while (jD > iD);
-            lds_pt<D>(xs + iD, xi);
-          }
-        }
-        lds_pt<D>(xs + jD, xj);
-        __builtin_nontemporal_store(pair_dist<D>(xi, xj), out + c0 + off + 64 * q);
+      for (int u = 0; u < 8; ++u)
+        if (m0 + u * kBatchThreads < len) v[u] = src[m0 + u * kBatchThreads];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (m0 + u * kBatchThreads < len) dst[m0 + u * kBatchThreads] = v[u];
+    }
+    have1 = q1;
+  };
+  // set s: its positions [s_beg, s_end), first point and number of points
+  uint64_t s_beg, s_end;
+  int64_t p0, n;
+  auto enter = [&]() {
+    s_beg = (uint64_t)oo[s];
+    s_end = (uint64_t)oo[s + 1];
+    p0 = point_off[s];
+    n = point_off[s + 1] - p0;
+  };
+  // goes on to the set of position e if it is not s
+  auto advance = [&]() {
+    if (e >= end || e < s_end) return;
+    do ++s;
+    while ((uint64_t)oo[s + 1] <= e);  // past empty sets
+    enter();
+  };
+  enter();
+  while (e < end) {
+    // chunks end on units: a full chunk's 256-byte stores then cover whole
+    // lines (non-temporal stores of split lines cost 1.3 times the time)
+    const uint32_t past = (uint32_t)(e - first) % kBatchUnit;
+    const uint64_t inside = s_end < end ? s_end : end;
+    // what the full chunks of set s may take (a set smaller than a chunk
+    // shares one with its neighbours)
+    const uint64_t room = s_end - s_beg >= kBatchChunk && n <= kBatchLdsFloats / D ? inside - e : 0;
+    if (past == 0 && room >= kBatchQuarter) {
+      if (p0 < have0 || p0 + n > have1) {
+        __syncthreads();  // every wave is done with the previous points
+        stage(p0, p0 + n);
+        __syncthreads();
       }
+      const float *xp = xs + (uint32_t)(p0 - have0) * D;
+      if (room >= kBatchChunk) {
+        set_chunk<D, kBatchPer>(xp, (uint32_t)(e - s_beg), out + e, w, l);
+        e += kBatchChunk;
+      } else {
+        set_chunk<D, kBatchPer / 4>(xp, (uint32_t)(e - s_beg), out + e, w, l);
+        e += kBatchQuarter;
+      }
+      advance();
       continue;
     }
-#pragma unroll 1
-    for (int q = 0; q < kBatchPer; ++q) {
-      const uint64_t e = c0 + off + 64 * q;
-      if (e >= total) break;
-      int32_t sl = s;
-      while ((uint64_t)oo[sl + 1] <= e) ++sl;
-      uint64_t i, j;
-      g_lambda64(e - (uint64_t)oo[sl], i, j);
-      const float *__restrict__ Xl = X + point_off[sl] * D;
-      float xi[D], xj[D];
-      load_pt<D>(Xl, D, i, xi);
-      load_pt<D>(Xl, D, j, xj);
-      __builtin_nontemporal_store(pair_dist<D>(xi, xj), out + e);
+    // as many sets from s on as start before the limit and fit; the limit is
+    // the next unit if full chunks of set s follow, the one after the end of
+    // set s if full chunks of the next set do
+    uint64_t lim = e - past + kBatchMulti;
+    if (room >= kBatchUnit - past + kBatchQuarter)
+      lim = e - past + kBatchUnit;
+    else if (s + 2 <= S && (uint64_t)oo[s + 2] - s_end >= (uint64_t)(kBatchChunk + kBatchUnit))
+      lim = s_end + (kBatchUnit - 1 - (s_end - first + kBatchUnit - 1) % kBatchUnit);
+    if (lim > end) lim = end;
+    const int64_t k = (int64_t)s + t;
+    int64_t o = 0, o1 = 0, p = 0, p1 = 0;
+    bool fits = false;
+    if (k < S) {
+      o = oo[k];
+      o1 = oo[k + 1];
+      p = point_off[k];
+      p1 = point_off[k + 1];
+      fits = (uint64_t)o < lim && p1 - p0 <= kBatchLdsFloats / D;
     }
+    const int32_t count = __syncthreads_count(fits);
+    if (count == 0) {
+      // set s is too large for LDS
+      const uint64_t stop = s_end < lim ? s_end : lim;
+      const float *__restrict__ Xl = X + p0 * D;
+      for (uint64_t pos = e + t; pos < stop; pos += kBatchThreads) {
+        uint64_t i, j;
+        g_lambda64(pos - s_beg, i, j);
+        float xi[D], xj[D];
+        load_pt<D>(Xl, D, i, xi);
+        load_pt<D>(Xl, D, j, xj);
+        __builtin_nontemporal_store(pair_dist<D>(xi, xj), out + pos);
+      }
+      e = stop;
+      advance();
+      continue;
+    }
+    stage(p0, point_off[s + count]);
+    if ((int32_t)t < count) {
+      tab_o[t] = (int32_t)(o - (int64_t)e);
+      tab_p[t] = (int32_t)(p - have0);
+      if ((int32_t)t == count - 1) tab_o[count] = (int32_t)(o1 - (int64_t)e);
+    }
+    __syncthreads();
+    const uint64_t last = (uint64_t)oo[s + count];
+    const int32_t len = (int32_t)((last < lim ? last : lim) - e);
+    // the lanes sit on multiples of 64 positions, the first of them up to 63
+    // before e
+    const int32_t shift = (int32_t)(past % 64);
+    const int32_t per = (len + shift + kBatchThreads - 1) / kBatchThreads;
+    const int32_t begin = (int32_t)(w * 64) * per - shift;
+    const int32_t stop = begin + 64 * per < len ? begin + 64 * per : len;
+    int32_t pos = begin + (int32_t)l;
+    if (pos < 0) pos += 64;
+    if (pos < stop) {
+      int32_t a = 0, b = count;  // largest a with tab_o[a] <= pos
+      while (b - a > 1) {
+        const int32_t mid = (a + b) >> 1;
+        if (tab_o[mid] <= pos) a = mid; else b = mid;
+      }
+      float *__restrict__ op = out + e;
+      int32_t beg = tab_o[a], next = tab_o[a + 1];
+      const float *xp = xs + (uint32_t)tab_p[a] * D;
+      // four positions at a time, each mapped on its own: no step waits for
+      // the one before it (rows are short here, so stepping from row to row
+      // would loop, and lanes would wait for one another)
+      constexpr int R = 4;
+      for (; pos < stop; pos += 64 * R) {
+        float xi[R][D], xj[R][D];
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+          // (past the stretch: its last position, not stored)
+          const int32_t at = pos + 64 * u < stop ? pos + 64 * u : stop - 1;
+          if (at >= next) {
+            do {
+              ++a;
+              beg = next;
+              next = tab_o[a + 1];
+            } while (next <= at);
+            xp = xs + (uint32_t)tab_p[a] * D;
+          }
+          uint32_t i, j;
+          g_lambda_small((uint32_t)(at - beg), i, j);
+          lds_pt<D>(xp + i * D, xi[u]);
+          lds_pt<D>(xp + j * D, xj[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < R; ++u)
+          if (pos + 64 * u < stop)
+            __builtin_nontemporal_store(pair_dist<D>(xi[u], xj[u]), op + pos + 64 * u);
+      }
+    }
+    e += (uint64_t)len;
+    if (count > 1) {
+      s += count - 1;  // the last set of the chunk
+      enter();
+    }
+    advance();
   }
 }
 
