@@ -213,13 +213,25 @@ def tdmap_last_error() -> str:
 # torch conveniences
 # ---------------------------------------------------------------------------
 
+_torch_module = None
+
+
 def _torch():
-    import torch
-    return torch
+    global _torch_module
+    if _torch_module is None:
+        import torch
+        _torch_module = torch
+    return _torch_module
 
 
 def _stream() -> int:
-    return _torch().cuda.current_stream().cuda_stream
+    """torch's current stream of the current device.  The handle is read
+    without building a Stream object, which costs 3 us a call (4 to 16 in
+    autograd's thread) against 0.3."""
+    torch = _torch()
+    if torch.cuda.is_initialized():
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _points(X):
@@ -251,6 +263,20 @@ def _device_tensor(t, name: str, dtype, device, min_numel: int = 0,
     if t.numel() < min_numel:
         raise ValueError(f"{name} must hold at least {min_numel} elements, got {t.numel()}")
     return t
+
+
+def _workspace(workspace, device, *what):
+    """(tensor, pointer, bytes): the caller's workspace, or a new one of the
+    size tdmap_workspace_size(*what) asks for (none if that is 0).  The tensor
+    is to be kept until the call is issued."""
+    if workspace is None:
+        size = tdmap_workspace_size(*what)
+        if size == 0:
+            return None, 0, 0
+        torch = _torch()
+        workspace = torch.empty(size, dtype=torch.uint8, device=device)
+        return workspace, workspace.data_ptr(), size
+    return workspace, workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
 
 def _triangle_cells(N: int, layout: int) -> int:
@@ -357,11 +383,9 @@ def edm(X, layout: str = "full", strategy: str = "ltm", rho: int = 0,
     else:
         _device_tensor(out, "out", torch.float32, X.device,
                        min_numel=_triangle_cells(N, lay))
-    ws_bytes = tdmap_workspace_size(OP_EDM, N, d, 0, rho, prec)
-    if ws_bytes and workspace is None:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=X.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else 0
-    ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    ws_ptr, ws_len = 0, 0
+    if prec != FP32 or workspace is not None:  # FP32 takes none
+        workspace, ws_ptr, ws_len = _workspace(workspace, X.device, OP_EDM, N, d, 0, rho, prec)
     tdmap_edm(X.data_ptr(), N, d, X.stride(0), out.data_ptr(), ldd, lay,
               STRATEGIES[strategy], rho, prec, ws_ptr, ws_len, _stream())
     return out
@@ -391,11 +415,7 @@ def edm_shard(X, shard: int, num_shards: int, layout: str = "full", rho: int = 2
     else:
         _device_tensor(out, "out", torch.float32, X.device,
                        min_numel=_triangle_cells(N, lay))
-    ws_bytes = tdmap_workspace_size(OP_EDM, N, d, 0, rho, prec)
-    if ws_bytes and workspace is None:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=X.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else 0
-    ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    workspace, ws_ptr, ws_len = _workspace(workspace, X.device, OP_EDM, N, d, 0, rho, prec)
     tdmap_edm_shard(X.data_ptr(), N, d, X.stride(0), out.data_ptr(), ldd, lay, LTM, rho, prec,
                     ws_ptr, ws_len, shard, num_shards, _stream())
     return out
@@ -413,11 +433,7 @@ def gram_recompute_count(X, precision: str = "bf16_gram", rho: int = 0, out=None
     if out is None:
         out = torch.empty(packed_size(N), dtype=torch.float32, device=X.device)
     _device_tensor(out, "out", torch.float32, X.device, min_numel=packed_size(N))
-    ws_bytes = tdmap_workspace_size(OP_EDM, N, d, 0, rho, prec)
-    if ws_bytes and workspace is None:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=X.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else 0
-    ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    workspace, ws_ptr, ws_len = _workspace(workspace, X.device, OP_EDM, N, d, 0, rho, prec)
     count = torch.empty(1, dtype=torch.int64, device=X.device)
     tdmap_gram_recompute_count(X.data_ptr(), N, d, X.stride(0), out.data_ptr(), prec, rho,
                                ws_ptr, ws_len, count.data_ptr(), _stream())
@@ -441,11 +457,7 @@ def edm_backward(X, dD, layout: str = "packed", rho: int = 0, deterministic: boo
     else:
         _device_tensor(dD, "dD", torch.float32, X.device, min_numel=_triangle_cells(N, lay))
     det = 1 if deterministic else 0
-    ws_bytes = tdmap_workspace_size(OP_BACKWARD, N, d, 0, rho, det)
-    if ws_bytes and workspace is None:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=X.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else 0
-    ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    workspace, ws_ptr, ws_len = _workspace(workspace, X.device, OP_BACKWARD, N, d, 0, rho, det)
     tdmap_edm_backward(X.data_ptr(), N, d, X.stride(0), dD.data_ptr(), ldd, lay,
                        out.data_ptr(), rho, det, ws_ptr, ws_len, _stream())
     return out
@@ -474,11 +486,7 @@ def stress_backward(X, delta, layout: str = "packed", rho: int = 0,
         _device_tensor(delta, "delta", torch.float32, X.device,
                        min_numel=_triangle_cells(N, lay))
     det = 1 if deterministic else 0
-    ws_bytes = tdmap_workspace_size(OP_STRESS, N, d, 0, rho, det)
-    if ws_bytes and workspace is None:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=X.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else 0
-    ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    workspace, ws_ptr, ws_len = _workspace(workspace, X.device, OP_STRESS, N, d, 0, rho, det)
     delta_ptr = delta.data_ptr() if delta.numel() else 0
     tdmap_stress_backward(X.data_ptr(), N, d, X.stride(0), delta_ptr, ldd, lay,
                           out.data_ptr(), loss.data_ptr(), rho, det, ws_ptr, ws_len,
@@ -506,11 +514,12 @@ def edm_batched(X_cat, point_off, out_off, rho: int = 0, out=None, workspace=Non
     # the size of out against out_off[S] would need a synchronising read of
     # the device offsets: only its type, device and contiguity are checked
     _device_tensor(out, "out", torch.float32, X_cat.device)
-    ws_bytes = tdmap_workspace_size(OP_BATCHED, 0, d, S, rho, 0)
-    if ws_bytes and workspace is None:
-        workspace = torch.empty(ws_bytes, dtype=torch.uint8, device=X_cat.device)
-    ws_ptr = workspace.data_ptr() if workspace is not None else 0
-    ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
+    if rho == 0 and S > 0:
+        # the library reads point_off[S] back to look its decision up by the
+        # mean set size (18 us and a wait for the stream); the rows of X_cat
+        # give the same size without it (any decision is a right answer)
+        rho = tdmap_tuned_rho(OP_BATCHED, 0, X_cat.shape[0] // S, d, S)
+    workspace, ws_ptr, ws_len = _workspace(workspace, X_cat.device, OP_BATCHED, 0, d, S, rho, 0)
     tdmap_edm_batched(X_cat.data_ptr(), d, S, point_off.data_ptr(), out_off.data_ptr(),
                       out.data_ptr(), rho, ws_ptr, ws_len, _stream())
     return out
