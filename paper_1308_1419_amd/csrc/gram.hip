@@ -24,8 +24,8 @@
 //     compact window of the packed output and small N makes more
 //     work-groups.
 // Measured (us, blocks / strips, prologue included): N = 100000, d = 64
-// 4390 / 3920 (BF16), 5290 / 5050 (split); N = 50000, d = 256 1580 / 1940;
-// N = 30011, d = 200 split 805 / 880; N = 2000, d = 100 16.7 / 12.2.  The
+// 4570 / 3920 (BF16), 4740 / 5050 (split); N = 50000, d = 256 1480 / 1940;
+// N = 30011, d = 200 split 700 - 732 / 880; N = 2000, d = 100 16 / 12.2.  The
 // autotuner times both.  With row-major operands, staged through LDS in the
 // strips and loaded by every lane on its own in 128 x 128 tiles, the same
 // sizes took, in the faster of the two, 4400, 6640, 2946, 1860 and 15.3 us.
@@ -170,13 +170,16 @@ __device__ __forceinline__ float exact_dist8(const float *__restrict__ X, int64_
 __device__ __forceinline__ int acc_row(int v, int l) { return (v >> 2) * 8 + (l >> 5) * 4 + (v & 3); }
 
 // The epilogue of one pair from its accumulator and the two squared norms:
-// sqrt(G), and the lane's bit of `low` set for a pair to be recomputed (its
+// G (or sqrt(G)), and the lane's bit of `low` set for a pair to be recomputed (its
 // square root, possibly of a negative G, is replaced then).
-__device__ __forceinline__ float gram_value(float acc, float ni, float nj, uint64_t &low) {
+__device__ __forceinline__ float gram_square(float acc, float ni, float nj, uint64_t &low) {
   const float sn = ni + nj;
   const float G = __builtin_fmaf(-2.0f, acc, sn);
   low |= __builtin_amdgcn_ballot_w64(G <= kGramTheta * sn);
-  return __builtin_amdgcn_sqrtf(G);
+  return G;
+}
+__device__ __forceinline__ float gram_value(float acc, float ni, float nj, uint64_t &low) {
+  return __builtin_amdgcn_sqrtf(gram_square(acc, ni, nj, low));
 }
 // Whether it is one of those.
 __device__ __forceinline__ bool gram_close(float acc, float ni, float nj) {
@@ -367,7 +370,6 @@ __global__ __launch_bounds__(512, 4) void gram_block_kernel(GramArgs a, uint32_t
     // for the loads in flight; the empty asm keeps the LDS reads below)
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    if (s + 2 < stages) load_stage(s + 2);
     const unsigned char *buf = ops + (s % 3) * kBlkStage;
     bf16x8 av[2][2], bv[2][2];  // [block][k-step or part]
 #pragma unroll
@@ -377,6 +379,9 @@ __global__ __launch_bounds__(512, 4) void gram_block_kernel(GramArgs a, uint32_t
         av[x][h] = lds_fragment(buf, 2 * (2 * wr + x) + h);
         bv[x][h] = lds_fragment(buf, 2 * (kBlkRows / 32 + 2 * wc + x) + h);
       }
+    // (behind the LDS reads in the queues they share: 732 us against 750 with
+    // N = 30011, d = 200 split)
+    if (s + 2 < stages) load_stage(s + 2);
     if constexpr (SPLIT) {
 #pragma unroll
       for (int p = 0; p < 3; ++p)
@@ -399,48 +404,62 @@ __global__ __launch_bounds__(512, 4) void gram_block_kernel(GramArgs a, uint32_t
   }
   __syncthreads();  // the operands are read
 
-  // output: 32 rows x 64 columns at a time through the wave's own 8 KB of
-  // LDS, then whole rows of 64 cells (256 contiguous bytes per store)
+  // Output, 32 rows x 64 columns at a time, in whole rows of 64 cells (256
+  // contiguous bytes per store).  Accumulator v of the two column blocks holds
+  // the halves of rows R and R + 4: one swap of wave halves makes each a row of
+  // 64 columns, stored from the register.  Blocks with pairs to recompute, at
+  // the diagonal or past the last point go through the wave's own 8 KB of LDS
+  // instead (when all of them did: 788 us against 750, same case; LDS feeds
+  // the products too).
   float *st = reinterpret_cast<float *>(ops) + q * 32 * 64;
   uint32_t nrec = 0;
 #pragma unroll
   for (int x = 0; x < 2; ++x) {
     const int64_t rw = r0 + 64 * wr + 32 * x;
     if (rw >= N || cw > rw + 31) continue;  // no cell of the triangle (uniform)
+    const bool edge = cw + 63 > rw || rw + 32 > N;
     uint64_t low = 0;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
-      const int rr = acc_row(v, l);
-      const float ni = nrow[64 * wr + 32 * x + rr];
+      const float ni = nrow[64 * wr + 32 * x + acc_row(v, l)];
 #pragma unroll
       for (int y = 0; y < 2; ++y) {
         const float e = acc[x][y][v];  // (copied out: a bit cast of a vector element is avoided)
-        st[rr * 64 + 32 * y + lr] = gram_value(e, ni, nc[y], low);
+        acc[x][y][v] = gram_square(e, ni, nc[y], low);
       }
     }
-    if (low != 0) {
-      uint32_t mask = 0;
-#pragma unroll
-      for (int m = 0; m < 32; ++m) {
-        const float e = acc[x][m >> 4][m & 15];
-        mask |= (uint32_t)gram_close(e, nrow[64 * wr + 32 * x + acc_row(m & 15, l)], nc[m >> 4]) << m;
-      }
-      recompute_close<COUNT, 32>(
-          a, list[q], mask, cw + 63 >= rw || rw + 32 > N, rw, cw,
-          [&](int m) { return acc_row(m & 15, l) * 256 + 32 * (m >> 4) + lr; },
-          [&](int p) { return st + (p >> 8) * 64 + (p & 255); }, nrec);
-    }
-    __builtin_amdgcn_wave_barrier();  // the wave reads its own LDS writes
     // row rw + r starts at T(rw) + r rw + r (r + 1) / 2
-    float *__restrict__ o = a.D + tri64((uint64_t)rw) + (uint64_t)cw + l;
+    float *__restrict__ o = a.D + tri64((uint64_t)rw) + (uint64_t)cw;
     const uint32_t rwu = (uint32_t)rw;
-    if (cw + 63 <= rw && rw + 32 <= N) {
-#pragma unroll 8
-      for (uint32_t r = 0; r < 32; ++r) o[r * rwu + ((r * (r + 1)) >> 1)] = st[r * 64 + l];
-    } else {
-      for (uint32_t r = 0; r < 32; ++r)
-        if (rw + r < N && cw + l <= rw + r) o[r * rwu + ((r * (r + 1)) >> 1)] = st[r * 64 + l];
+    if (low == 0 && !edge) {
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const float e0 = acc[x][0][v], e1 = acc[x][1][v];
+        const auto w2 = __builtin_amdgcn_permlane32_swap(
+            __builtin_bit_cast(uint32_t, __builtin_amdgcn_sqrtf(e0)),
+            __builtin_bit_cast(uint32_t, __builtin_amdgcn_sqrtf(e1)), false, false);
+        const uint32_t b0 = w2[0], b1 = w2[1];
+        const uint32_t r = (v >> 2) * 8 + (v & 3);
+        (o + r * rwu + ((r * (r + 1)) >> 1))[l] = __builtin_bit_cast(float, b0);
+        (o + (r + 4) * rwu + (((r + 4) * (r + 5)) >> 1))[l] = __builtin_bit_cast(float, b1);
+      }
+      continue;
     }
+    uint32_t mask = 0;
+#pragma unroll
+    for (int m = 0; m < 32; ++m) {
+      const int rr = acc_row(m & 15, l);
+      const float G = acc[x][m >> 4][m & 15];
+      mask |= (uint32_t)(G <= kGramTheta * (nrow[64 * wr + 32 * x + rr] + nc[m >> 4])) << m;
+      st[rr * 64 + 32 * (m >> 4) + lr] = __builtin_amdgcn_sqrtf(G);
+    }
+    if (low != 0)
+      recompute_close<COUNT, 32>(
+          a, list[q], mask, edge, rw, cw, [&](int m) { return acc_row(m & 15, l) * 256 + 32 * (m >> 4) + lr; },
+          [&](int p) { return st + (p >> 8) * 64 + (p & 255); }, nrec);
+    __builtin_amdgcn_wave_barrier();  // the wave reads its own LDS writes
+    for (uint32_t r = 0; r < 32; ++r)
+      if (rw + r < N && cw + l <= rw + r) (o + r * rwu + ((r * (r + 1)) >> 1))[l] = st[r * 64 + l];
     __builtin_amdgcn_wave_barrier();
   }
   if (COUNT && nrec) atomicAdd(a.rec_count, (unsigned long long)nrec);
