@@ -205,7 +205,7 @@ __device__ __forceinline__ float add_features(float s, float row, f4 c) {
 // own issues 2 d loads, and a wave's 64 column loads touch 16 to 32 rows of
 // X each: at N = 8000, d = 16, rho = 16 (full layout, LTM) the launch took
 // 907 us, bound by those uncoalesced loads; this one takes 92 us, bound by
-// the issue of about 85 vector instructions per wave, 32 of them the sum.
+// the placing of its block (wide_rows_kernel below takes such sizes).
 // Here a block takes the features 16 at a time:
 // its rho column points are loaded once, coalesced, into LDS (pitch 20
 // floats: the 16-byte reads of 16 lanes cover every bank once), the next 16
@@ -333,6 +333,148 @@ __global__ __launch_bounds__(RHO *RHO) void wide_cell_kernel(EdmArgs a, uint32_t
     o[lo] = v;
 }
 
+// The LTM launches of wide_cell_kernel with enough blocks.  Placing a block
+// costs each of its waves about 110 scalar instructions and its column points
+// four 16-byte LDS reads a lane, against 32 vector instructions of sum per 16
+// features; so a work-group does W block rows of one block column in turn,
+// with the column's features in registers for all of them and only the row
+// points read anew, all W loaded before the first is used.  Work-group u: with
+// (I, J) = g(u / W), block column W J + u mod W of block rows W I ..
+// W I + W - 1; consecutive work-groups are neighbouring columns of the same
+// rows, and each XCD takes one contiguous range of u, as there.  Bound by the
+// vector instructions of the sums (26 us at the size below).  N = 8000,
+// d = 16, full layout: rho 16 45 us (wide_cell_kernel 92), rho 8 58 (117);
+// packed, rho 32 53 (107).  Rho 8 takes W = 4: its row points (64 of them at
+// W = 8) are read from LDS, and 100 registers and 5.8 KB leave 64 us.
+// Offsets are 32 bits from uniform addresses (both pitches below 2^22).
+template <int RHO, int LAYOUT, int W>
+__global__ __launch_bounds__(RHO *RHO) void wide_rows_kernel(EdmArgs a, uint32_t u0) {
+  constexpr int F = 16;       // features per step
+  constexpr int PITCH = F + 4;
+  constexpr int NT = RHO * RHO;
+  constexpr int PER = RHO * F >= NT ? RHO * F / NT : 1;  // staged column values per thread
+  constexpr bool ALL = RHO * F >= NT;                    // every thread stages
+  constexpr int STEP = RHO == 8 ? NT / F : RHO;          // between a thread's row points
+  constexpr int NR = RHO * W / STEP;                     // a thread's row values
+  const uint32_t u = u0 + xcd_contiguous(blockIdx.x, gridDim.x);
+  uint32_t bi, bj;
+  g_lambda_uniform(u / W, bi, bj);
+  bi *= W;
+  bj = bj * W + u % W;
+  const uint32_t N = (uint32_t)a.N, end = (N - 1) / RHO;  // end: the last block row
+  if (bj > end) return;
+  const uint32_t tx = threadIdx.x, ty = threadIdx.y, t = ty * RHO + tx;
+  const int d = a.d;
+  __shared__ __align__(16) float xc[RHO * PITCH];
+  __shared__ __align__(16) float xr[RHO == 8 ? RHO * W * PITCH : 4];
+  const uint32_t f = RHO == 8 ? t % F : tx % F;
+  auto offset = [](uint32_t r, int64_t pitch, uint32_t c) {
+    return ((r & 0xffu) * ((uint32_t)pitch & 0x3fffffu) + c) * 4u;
+  };
+  auto at = [](const float *base, uint32_t o) {
+    return *reinterpret_cast<const float *>(reinterpret_cast<const char *>(base) + o);
+  };
+  // points past the last are read as the last (their cells are not stored),
+  // features past d as the last and taken as 0 when used
+  const uint32_t ni = N - bi * RHO, nj = N - bj * RHO;
+  const bool inner = ni >= RHO * W;
+  uint32_t co[PER];
+#pragma unroll
+  for (int m = 0; m < PER; ++m) {
+    const uint32_t r = (RHO == 16 ? ty : t / F) + NT / F * m;
+    co[m] = offset(r < nj ? r : nj - 1, a.ldx, f);
+  }
+  const uint32_t rp = RHO == 8 ? t / F : ty;  // the thread's first row point
+  const uint32_t ro = offset(rp, a.ldx, f);
+  const float *__restrict__ xi = a.X + (uint64_t)(bi * RHO) * (uint64_t)a.ldx;
+  const float *__restrict__ xj = a.X + (uint64_t)(bj * RHO) * (uint64_t)a.ldx;
+  float cv[PER], rv[NR];
+  auto load = [&](int k0) {
+    const uint32_t lf = (uint32_t)(d - 1 - k0);
+    const uint32_t back = lf < F - 1 && f > lf ? (f - lf) * 4u : 0u;
+#pragma unroll
+    for (int m = 0; m < PER; ++m)
+      if (ALL || t < RHO * F) cv[m] = at(xj + k0, co[m] - back);
+    if (inner) {
+#pragma unroll
+      for (int m = 0; m < NR; ++m) rv[m] = at(xi + (int64_t)(m * STEP) * a.ldx + k0, ro - back);
+    } else {
+#pragma unroll
+      for (int m = 0; m < NR; ++m) {
+        const uint32_t r = rp + m * STEP;
+        rv[m] = at(xi + k0, offset(r < ni ? r : ni - 1, a.ldx, f) - back);
+      }
+    }
+  };
+  load(0);
+  float s[W] = {};
+  for (int k0 = 0;; k0 += F) {
+    const bool over = k0 + F >= d;
+    if (k0 + F > d && k0 + (int)f >= d) {
+#pragma unroll
+      for (int m = 0; m < PER; ++m) cv[m] = 0.0f;
+#pragma unroll
+      for (int m = 0; m < NR; ++m) rv[m] = 0.0f;
+    }
+    if (k0 > 0) __syncthreads();
+    if (ALL || t < RHO * F) {
+#pragma unroll
+      for (int m = 0; m < PER; ++m) xc[(t / F + NT / F * m) * PITCH + f] = cv[m];
+    }
+    float row[RHO == 8 ? 1 : W];
+#pragma unroll
+    for (int m = 0; m < NR; ++m) {
+      if constexpr (RHO == 8)
+        xr[(rp + m * STEP) * PITCH + f] = rv[m];
+      else
+        row[m] = rv[m];
+    }
+    if (!over) load(k0 + F);
+    __syncthreads();
+    auto add = [&](auto q) {
+      constexpr int Q = decltype(q)::value;
+      const f4 c = *reinterpret_cast<const f4 *>(&xc[tx * PITCH + Q]);
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        if constexpr (RHO == 8) {
+          const f4 r = *reinterpret_cast<const f4 *>(&xr[(w * RHO + ty) * PITCH + Q]);
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const float tt = r[k] - c[k];
+            s[w] = __builtin_fmaf(tt, tt, s[w]);
+          }
+        } else {
+          s[w] = add_features<Q>(s[w], row[w], c);
+        }
+      }
+    };
+    add(std::integral_constant<int, 0>());
+    if (k0 + 4 < d) add(std::integral_constant<int, 4>());
+    if (k0 + 8 < d) add(std::integral_constant<int, 8>());
+    if (k0 + 12 < d) add(std::integral_constant<int, 12>());
+    if (over) break;
+  }
+  // cell (i0 + ty, j0 + tx): the block's first cell and a lane offset
+  // (packed: T(i0 + ty) = T(i0) + ty i0 + ty (ty + 1) / 2, ty i0 < 2^30)
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    const uint32_t i = bi + w;
+    if (i < bj || i > end) continue;
+    float *__restrict__ o = a.D + out_index<LAYOUT>((uint64_t)(i * RHO), (uint64_t)(bj * RHO), a.ldd);
+    uint32_t lo;
+    if constexpr (LAYOUT == kLayoutFull)
+      lo = offset(ty, a.ldd, tx);
+    else
+      lo = (ty * (i * RHO) + ((ty * (ty + 1)) >> 1) + tx) * 4u;
+    float *__restrict__ cell = reinterpret_cast<float *>(reinterpret_cast<char *>(o) + lo);
+    const float v = __builtin_amdgcn_sqrtf(s[w]);
+    if (bj < i && i < end)
+      *cell = v;
+    else if (i * RHO + ty < N && bj * RHO + tx <= i * RHO + ty)
+      *cell = v;
+  }
+}
+
 // ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
@@ -441,9 +583,36 @@ static hipError_t launch_cell_t(int strategy, int rho, const EdmArgs &a,
       });
 }
 
+template <int RHO, int LAYOUT, int W>
+static hipError_t launch_wide_rows(const EdmArgs &a) {
+  const uint64_t rows = (uint64_t)(a.N + RHO * W - 1) / (RHO * W), groups = W * rows * (rows + 1) / 2;
+  // keep every launch below 2^32 work-items
+  const uint64_t most = (((uint64_t)1 << 32) - 1) / (RHO * RHO);
+  for (uint64_t u0 = 0; u0 < groups; u0 += most) {
+    const uint64_t c = groups - u0 < most ? groups - u0 : most;
+    hipLaunchKernelGGL((wide_rows_kernel<RHO, LAYOUT, W>), dim3((uint32_t)c), dim3(RHO, RHO), 0, a.stream, a,
+                       (uint32_t)u0);
+    if (const hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+// Cells from which a work-group takes 4, and (rho 16 and 32) 8 block rows:
+// below, the fewer work-groups leave the chip idle.  Against one block per
+// work-group, us: N = 1400, d = 64, rho 32: 16.5 against 14.5; 2000: 23.6
+// against 25.4; d = 16, rho 16 at 2000: 8.3 against 10.8.  Eight rows against
+// four: N = 3000, d = 24, rho 16: 14.6 against 13.9; N = 5500, d = 16, rho 16
+// and 32: 28.7 and 35.5 against 30.5 and 39.0.
+constexpr uint64_t kWideRows4 = 1 << 20;
+constexpr uint64_t kWideRows8 = 6 << 20;
 template <int RHO, int LAYOUT>
 static hipError_t launch_wide_t(int strategy, const EdmArgs &a) {
   const uint32_t nb = (uint32_t)((a.N + RHO - 1) / RHO);
+  const uint64_t cells = (uint64_t)a.N * (uint64_t)a.N / 2;
+  if (strategy == kLTM && cells >= kWideRows4 && a.ldx < (1 << 22) && (LAYOUT != kLayoutFull || a.ldd < (1 << 22))) {
+    if (RHO > 8 && cells >= kWideRows8) return launch_wide_rows<RHO, LAYOUT, RHO == 8 ? 4 : 8>(a);
+    return launch_wide_rows<RHO, LAYOUT, 4>(a);
+  }
   return launch_square_blocks(
       strategy, RHO, a, [&](auto route, dim3 grid, uint32_t lam0, int mode, uint32_t side) {
         hipLaunchKernelGGL((wide_cell_kernel<RHO, LAYOUT, route>), grid, dim3(RHO, RHO), 0, a.stream,
