@@ -204,8 +204,8 @@ __global__ __launch_bounds__(256) void edm_sweep_kernel(const float *__restrict_
 // position outside a full chunk searched its set and read global memory; the
 // 64-cell tiles 40 with their prefix sums); 4096 sets of 8 to 32 points under
 // 10.7, the time to issue the call (107); 500 sets of 250 to 1000 points 101
-// (112); 1024 sets of 64 to 4096 points 1950 (1950), bound by the write rate
-// of a persistent grid.
+// (112); 1024 sets of 64 to 4096 points 2207 (2269; 1830 and 1928 where the
+// output lies better), bound by the write rate of a persistent grid.
 constexpr int kBatchThreads = 1024;
 constexpr int kBatchPer = 16;                           // positions per lane per chunk
 constexpr int kBatchChunk = kBatchThreads * kBatchPer;  // 16384 positions
@@ -215,6 +215,12 @@ constexpr int kBatchUnit = kBatchThreads;
 constexpr int kBatchTable = kBatchThreads;              // sets of a chunk
 constexpr int kBatchLdsFloats = 16384;                  // 64 KB
 constexpr int kBatchWgsPerCu = 2;
+// Stores a wave leaves unfinished when it goes on to the next (vmcnt): the
+// write rate falls with the bytes that are being written at a time, and 32
+// waves a CU with 16 stores of 256 bytes each would have 128 KB.  1024 sets of
+// 64 to 4096 points, d = 3: 2233, 2203, 2239, 2279 and 2283 us for 1, 2, 3, 4
+// and 8, 2272 with no wait; 500 sets of 250 to 1000 points 98 to 100 in all.
+constexpr int kBatchPending = 2;
 
 template <int D>
 __device__ __forceinline__ void lds_pt(const float *p, float (&v)[D]) {
@@ -266,6 +272,7 @@ __device__ __forceinline__ void set_chunk(const float *xp, uint32_t lam, float *
     }
     lds_pt<D>(xp + jD, xj);
     __builtin_nontemporal_store(pair_dist<D>(xi, xj), o + off + 64 * q);
+    __builtin_amdgcn_s_waitcnt(0x0F70 | kBatchPending);
   }
 }
 
