@@ -316,9 +316,9 @@ int tdmap_stress_backward(const float *X, int64_t N, int32_t d, int64_t ldx,
  *              written).
  *   rho        1: one-cell blocks: a persistent grid sweeps the
  *              concatenated packed output; each work-group owns one
- *              contiguous stretch of 16384-position chunks and reads a set's
- *              points from LDS (sets of up to 16384 / d points; larger sets
- *              read global memory);
+ *              contiguous stretch and reads the points from LDS, of one set
+ *              or of as many as its chunk covers (sets of up to 16384 / d
+ *              points; larger sets read global memory);
  *              64 or 128: a persistent grid walks TS x TS tiles in
  *              contiguous ranges;
  *              0: autotuned.
