@@ -122,7 +122,9 @@ int tdmap_map_blocks_nodiag(uint64_t lambda0, uint64_t count, uint32_t *ij, void
  *                          written as one linear sweep, four positions per
  *                          thread;
  *              8, 16, 32 : rho x rho threads per block, one cell per thread,
- *                          as the paper launches every strategy;
+ *                          as the paper launches every strategy (LTM with
+ *                          d > 4 and N^2 / 2 >= 2^20: four or eight block
+ *                          rows of one block column per work-group);
  *              64, 128  : (LTM, BB) rho x rho cell tiles per 256-thread
  *                          work-group (full layout: four consecutive cells
  *                          per thread and row; packed layouts: one cell per

@@ -4,6 +4,10 @@
 // bit-identical values).  The maps are arithmetic only: no lookup tables,
 // no auxiliary global memory (the restriction of Sec. III-B).
 //
+// With more than four features, LTM, BB and REC blocks stage their points
+// (wide_cell_kernel), and large LTM launches give a work-group several
+// blocks of one block column (wide_rows_kernel).
+//
 // Each kernel has two twins that evaluate the same map and filters: one
 // counts blocks / fully idle blocks / idle threads instead of storing, the
 // other is the paper's dummy kernel (Sec. III-A, Sec. IV), which measures
