@@ -161,6 +161,15 @@ __global__ __launch_bounds__(256) void edm_tile_kernel(EdmArgs a, uint32_t lam0)
 //   full                312 311 292 291   before 326 330 328 331
 //   full, ldd odd       350   - 350 353   before 828 829 837 844
 //   packed              272 271 271 272   before 286 288 278 292
+//
+// LTM leaves out the strips past the last point, up to a whole tile row less
+// one strip (a fifth of the launch at 7200 points in 1024-column tiles).  With /
+// without them, d = 1, 3: full, N = 4097 (1024 columns) 11.4 / 9.5 and 10.1 /
+// 8.6 us, N = 6400 20.9 / 18.1 and 18.7 / 16.2; packed, N = 7200 19.7 / 17.7 and
+// 19.9 / 18.0, N = 40000 494 / 484 and 489 / 480.  The aligned full layout keeps
+// them above kBandWhole, where they leave the last of the eight XCDs with less
+// to write and the others write faster: N = 9217 35.2 / 36.7 and 35.2 / 37.5,
+// N = 22000 173 / 169 and 159 / 165, N = 8500 30.7 / 30.0 and 30.9 / 30.8.
 template <int LAYOUT, bool VEC, int D>
 struct BandShape {
   // The strip is widest where rows are written end to end; packed rows are
@@ -178,7 +187,10 @@ struct BandShape {
   // 160 KB of LDS in 2 KB steps, kPerCu to 8 work-groups of it
   static constexpr int kIdleLds = kPerCu == 8 ? 0 : (160 / kPerCu / 2 * 2 - 1) * 1024;
 };
-constexpr uint64_t kBandSmall = (uint64_t)64 << 20;  // output bytes
+// Lines of the rules, in bytes of cells (4 N (N + 1) / 2).
+constexpr uint64_t kBandSmall = (uint64_t)64 << 20;   // N = 5793
+constexpr uint64_t kBandWhole = (uint64_t)144 << 20;  // N = 8689
+static uint64_t band_bytes(const EdmArgs &a) { return 2 * (uint64_t)a.N * ((uint64_t)a.N + 1); }
 
 template <int D, int LAYOUT, bool VEC, bool BB, bool DENSE>
 __global__ __launch_bounds__(256) void edm_band_kernel(const float *__restrict__ X, uint32_t N,
@@ -268,16 +280,20 @@ __global__ __launch_bounds__(256) void edm_band_kernel(const float *__restrict__
 template <int D, int LAYOUT, bool VEC, bool DENSE>
 static hipError_t launch_band_t(bool bb, const EdmArgs &a) {
   using B = BandShape<LAYOUT, VEC, D>;
-  const uint64_t nb = (uint64_t)((a.N + B::W - 1) / B::W);
   const uint64_t N = (uint64_t)a.N;
-  const uint32_t lds = N * (N + 1) * 2 >= kBandSmall ? B::kIdleLds : 0;
+  const uint64_t nb = (N + B::W - 1) / B::W;
+  const uint32_t lds = band_bytes(a) >= kBandSmall ? B::kIdleLds : 0;
   if (bb) {
     hipLaunchKernelGGL((edm_band_kernel<D, LAYOUT, VEC, true, DENSE>),
                        dim3((uint32_t)(B::S * nb), (uint32_t)nb), dim3(256), lds, a.stream, a.X,
                        (uint32_t)a.N, a.ldx, a.D, a.ldd, 0u);
     return hipGetLastError();
   }
-  const uint64_t W = B::S * (nb * (nb + 1) / 2);
+  // strips of the last tile row: those past the last point end the range of w
+  // and are left out, except from a large aligned full output
+  const uint64_t left = N - (nb - 1) * B::W;
+  const uint64_t last = VEC && band_bytes(a) >= kBandWhole ? B::S : (left + B::H - 1) / B::H;
+  const uint64_t W = B::S * (nb * (nb - 1) / 2) + last * nb;
   if (W > 0xffffffffull) return hipErrorInvalidValue;  // w is 32-bit (N above 4 million)
   uint64_t lo, hi;
   shard_range(W, a.shard, a.nshards, lo, hi);
@@ -294,8 +310,8 @@ static hipError_t launch_band_t(bool bb, const EdmArgs &a) {
 
 template <int D, int LAYOUT, bool VEC>
 static hipError_t launch_band(bool bb, const EdmArgs &a) {
-  return a.ldx == D ? launch_band_t<D, LAYOUT, VEC, true>(bb, a)
-                    : launch_band_t<D, LAYOUT, VEC, false>(bb, a);
+  const bool dense = a.ldx == D;
+  return dense ? launch_band_t<D, LAYOUT, VEC, true>(bb, a) : launch_band_t<D, LAYOUT, VEC, false>(bb, a);
 }
 
 template <int TS, int D, int LAYOUT, bool VEC>
