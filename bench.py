@@ -628,8 +628,8 @@ def main():
     stream_gbs = bytes_alg / (t_stream * 1e-3) / 1e9
     traffic = stored_traffic()
     # the kernel's template arguments: feature count, layout (0 = full),
-    # 16-byte stores, BB grid, dense points
-    kname = (f"edm_band_kernel<{d}, 0, true, false, true>" if ts_ltm == 256
+    # 16-byte stores, narrow strips, BB grid, dense points
+    kname = (f"edm_band_kernel<{d}, 0, true, false, false, true>" if ts_ltm == 256
              else f"edm_tile_kernel<{ts_ltm}, {d}, 0, true, false>")
     if traffic and not traffic["kernel"].startswith(kname):
         traffic = None  # the counters were taken on another tile kernel

@@ -133,9 +133,10 @@ int tdmap_map_blocks_nodiag(uint64_t lambda0, uint64_t count, uint32_t *ij, void
  *                          lambda;
  *              256       : (LTM, BB) strips of 2 to 8 rows of W x W tiles,
  *                          2048 cells per 256-thread work-group; W = 1024
- *                          (512 for d = 4) where D is 16-byte aligned and
- *                          ldd a multiple of 4 (full layout), 256 in any
- *                          other full layout, 512 in the packed layouts.
+ *                          (512 for d = 4, 256 below N = 4579) where D is
+ *                          16-byte aligned and ldd a multiple of 4 (full
+ *                          layout), 256 in any other full layout, 512 in the
+ *                          packed layouts.
  *                          LTM: the tile row comes from g(lambda) on the
  *                          strip index divided by the strips per tile, and
  *                          the strips of a tile row are taken strip by strip

@@ -152,15 +152,29 @@ __global__ __launch_bounds__(256) void edm_tile_kernel(EdmArgs a, uint32_t lam0)
 // columns per work-group at 8, 6, 5 and 4 work-groups per CU (full layout);
 // a linear fill of as many bytes as the cells takes 253 to 270 us.  Hence the
 // wide, low strips, and hence fewer work-groups per CU than would fit, by
-// dynamic LDS that no thread uses, once the output is larger than the caches
-// take (kBandSmall).  One row per wave loses more to the loads of its column
-// points, which then serve four cells per lane, than it gains: 342 (full)
-// and 360 us (packed) against 292 and 271.
+// dynamic LDS that no thread uses, once the output is large (kCached).
+// One row per wave loses more to the loads of its column points, which then
+// serve four cells per lane, than it gains: 342 (full) and 360 us (packed)
+// against 292 and 271.
 // Measured at N = 30000 (us; before: 256-column strips of 8 rows at full
 // residency, and 256-cell tiles for an unaligned full layout), d = 1, 2, 3, 4:
 //   full                312 311 292 291   before 326 330 328 331
 //   full, ldd odd       350   - 350 353   before 828 829 837 844
 //   packed              272 271 271 272   before 286 288 278 292
+// and at other sizes (us), full residency / kPerCu, d = 1, 3:
+//   full, N = 8192      22.9 / 24.8   23.1 / 23.0
+//   full, N = 11585     58.6 / 54.4   59.2 / 56.1
+//   full, N = 46000     722 / 705     712 / 656
+//   packed, N = 5793    13.5 / 13.5   13.7 / 13.5
+//   packed, N = 16384   87.9 / 86.2   89.1 / 87.6
+//   packed, N = 46000   651 / 644     629 / 614
+//
+// Up to kBandNarrow the aligned full layout takes strips of 256 columns: a
+// small output pays for the upper half of wide diagonal tiles and for the
+// longer column loads at its start.  256 against 1024 columns (d = 4: 512), d =
+// 1, 2, 3, 4: N = 2100 4.1 4.1 4.2 4.5 against 4.6 4.3 4.3 4.6 us; 4097 8.3 8.3
+// 8.5 9.2 against 9.5 8.4 8.6 9.5; beyond the line, 5000 12.0 12.0 12.0 12.4
+// against 11.4 11.8 12.0 12.5.
 //
 // LTM leaves out the strips past the last point, up to a whole tile row less
 // one strip (a fifth of the launch at 7200 points in 1024-column tiles).  With /
@@ -170,12 +184,13 @@ __global__ __launch_bounds__(256) void edm_tile_kernel(EdmArgs a, uint32_t lam0)
 // them above kBandWhole, where they leave the last of the eight XCDs with less
 // to write and the others write faster: N = 9217 35.2 / 36.7 and 35.2 / 37.5,
 // N = 22000 173 / 169 and 159 / 165, N = 8500 30.7 / 30.0 and 30.9 / 30.8.
-template <int LAYOUT, bool VEC, int D>
+template <int LAYOUT, bool VEC, int D, bool SMALL>
 struct BandShape {
   // The strip is widest where rows are written end to end; packed rows are
   // adjacent, and unaligned full rows gain nothing from width.  At d = 4 the
-  // column points of 1024 columns cost more than the width gives.
-  static constexpr int W = VEC ? (D == 4 ? 512 : 1024) : (LAYOUT == kLayoutFull ? 256 : 512);
+  // column points of 1024 columns cost more than the width gives.  SMALL: see
+  // above.
+  static constexpr int W = VEC ? (SMALL ? 256 : D == 4 ? 512 : 1024) : (LAYOUT == kLayoutFull ? 256 : 512);
   static constexpr int kAcross = W / 256;     // waves across a strip
   static constexpr int kDown = 4 / kAcross;   // rows written at a time
   static constexpr int kRows = 2;             // rows per wave
@@ -184,19 +199,22 @@ struct BandShape {
   // work-groups per CU for a large output: fewer where a work-group's loads
   // (D floats per column) are over sooner
   static constexpr int kPerCu = VEC ? (D == 4 ? 6 : 4) : (LAYOUT == kLayoutFull ? 8 : (D <= 2 ? 6 : 7));
+  // cells (bytes) from which they are fewer, N = 5793 or (d = 1, whose four
+  // work-groups lose more up to there) 8689: see above
+  static constexpr uint64_t kCached = (uint64_t)(VEC && D == 1 ? 144 : 64) << 20;
   // 160 KB of LDS in 2 KB steps, kPerCu to 8 work-groups of it
   static constexpr int kIdleLds = kPerCu == 8 ? 0 : (160 / kPerCu / 2 * 2 - 1) * 1024;
 };
 // Lines of the rules, in bytes of cells (4 N (N + 1) / 2).
-constexpr uint64_t kBandSmall = (uint64_t)64 << 20;   // N = 5793
+constexpr uint64_t kBandNarrow = (uint64_t)40 << 20;  // N = 4579
 constexpr uint64_t kBandWhole = (uint64_t)144 << 20;  // N = 8689
 static uint64_t band_bytes(const EdmArgs &a) { return 2 * (uint64_t)a.N * ((uint64_t)a.N + 1); }
 
-template <int D, int LAYOUT, bool VEC, bool BB, bool DENSE>
+template <int D, int LAYOUT, bool VEC, bool SMALL, bool BB, bool DENSE>
 __global__ __launch_bounds__(256) void edm_band_kernel(const float *__restrict__ X, uint32_t N,
                                                        int64_t ldx_, float *__restrict__ out,
                                                        int64_t ldd, uint32_t w0) {
-  using B = BandShape<LAYOUT, VEC, D>;
+  using B = BandShape<LAYOUT, VEC, D, SMALL>;
   constexpr uint32_t S = B::S;
   const int64_t ldx = DENSE ? D : ldx_;
   uint32_t I, J, k;
@@ -277,14 +295,14 @@ __global__ __launch_bounds__(256) void edm_band_kernel(const float *__restrict__
   }
 }
 
-template <int D, int LAYOUT, bool VEC, bool DENSE>
+template <int D, int LAYOUT, bool VEC, bool SMALL, bool DENSE>
 static hipError_t launch_band_t(bool bb, const EdmArgs &a) {
-  using B = BandShape<LAYOUT, VEC, D>;
+  using B = BandShape<LAYOUT, VEC, D, SMALL>;
   const uint64_t N = (uint64_t)a.N;
   const uint64_t nb = (N + B::W - 1) / B::W;
-  const uint32_t lds = band_bytes(a) >= kBandSmall ? B::kIdleLds : 0;
+  const uint32_t lds = band_bytes(a) >= B::kCached ? B::kIdleLds : 0;
   if (bb) {
-    hipLaunchKernelGGL((edm_band_kernel<D, LAYOUT, VEC, true, DENSE>),
+    hipLaunchKernelGGL((edm_band_kernel<D, LAYOUT, VEC, SMALL, true, DENSE>),
                        dim3((uint32_t)(B::S * nb), (uint32_t)nb), dim3(256), lds, a.stream, a.X,
                        (uint32_t)a.N, a.ldx, a.D, a.ldd, 0u);
     return hipGetLastError();
@@ -300,7 +318,7 @@ static hipError_t launch_band_t(bool bb, const EdmArgs &a) {
   const uint64_t max_blocks = (((uint64_t)1 << 32) - 1) / 256;
   for (uint64_t w0 = lo; w0 < hi; w0 += max_blocks) {
     const uint64_t c = hi - w0 < max_blocks ? hi - w0 : max_blocks;
-    hipLaunchKernelGGL((edm_band_kernel<D, LAYOUT, VEC, false, DENSE>), dim3((uint32_t)c), dim3(256), lds,
+    hipLaunchKernelGGL((edm_band_kernel<D, LAYOUT, VEC, SMALL, false, DENSE>), dim3((uint32_t)c), dim3(256), lds,
                        a.stream, a.X, (uint32_t)a.N, a.ldx, a.D, a.ldd, (uint32_t)w0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -311,7 +329,9 @@ static hipError_t launch_band_t(bool bb, const EdmArgs &a) {
 template <int D, int LAYOUT, bool VEC>
 static hipError_t launch_band(bool bb, const EdmArgs &a) {
   const bool dense = a.ldx == D;
-  return dense ? launch_band_t<D, LAYOUT, VEC, true>(bb, a) : launch_band_t<D, LAYOUT, VEC, false>(bb, a);
+  if (VEC && band_bytes(a) < kBandNarrow)
+    return dense ? launch_band_t<D, LAYOUT, VEC, VEC, true>(bb, a) : launch_band_t<D, LAYOUT, VEC, VEC, false>(bb, a);
+  return dense ? launch_band_t<D, LAYOUT, VEC, false, true>(bb, a) : launch_band_t<D, LAYOUT, VEC, false, false>(bb, a);
 }
 
 template <int TS, int D, int LAYOUT, bool VEC>
