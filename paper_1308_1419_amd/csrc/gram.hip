@@ -477,8 +477,10 @@ __global__ __launch_bounds__(512, 4) void gram_block_kernel(GramArgs a, uint32_t
 // u = 0 .. 8 (I + 1) - 1:
 //   - up to 64 features (split: 32): two bands of kStripBand strips, swept
 //     across the tile row with the strip inner, so that a band's rows are
-//     written end to end, and three work-groups per CU for large outputs (the fewer bytes being written at a time, the
-//     better: 4.16 ms with four; at two the loads are no longer hidden, 4.34);
+//     written end to end, and three work-groups per CU for large outputs (the
+//     fewer bytes being written at a time, the better: 4.16 ms with four; at two
+//     the loads are no longer hidden, 4.34).  N = 100000, d = 40: 3856 us, 4355
+//     in column groups; N = 20000 159 and 182;
 //   - more: column groups of kStripGroup tiles, group outer, strip next, tile
 //     inner: a group's column points then stay in L2 across its 8 strips,
 //     which the wider operands need more (d = 64 split: 5.05 ms, 5.25 in
@@ -503,6 +505,7 @@ constexpr int kStripBytes = kStripRows * kStripPitch * 4;
 constexpr int kStripFrags = kStripBytes / 1024;  // fragments that fit the area
 constexpr uint32_t kStripGroup = 8;
 constexpr uint32_t kStripBand = 4;
+// (KPC: the padded feature count of an instance; those up to 64 all have one)
 template <bool SPLIT, int KPC>
 constexpr bool kStripBands = KPC != 0 && KPC * (SPLIT ? 2 : 1) <= 64;
 constexpr uint32_t kStripIdleLds = 16 * 1024;               // leaves three work-groups per CU
@@ -673,6 +676,7 @@ static void launch_gram_strips(int KP, dim3 grid, hipStream_t stream, const Gram
   switch (KP) {
     case 16: return launch_strip_kernel<SPLIT, 16, COUNT>(grid, stream, a, w0);
     case 32: return launch_strip_kernel<SPLIT, 32, COUNT>(grid, stream, a, w0);
+    case 48: return launch_strip_kernel<SPLIT, 48, COUNT>(grid, stream, a, w0);
     case 64: return launch_strip_kernel<SPLIT, 64, COUNT>(grid, stream, a, w0);
     case 128: return launch_strip_kernel<SPLIT, 128, COUNT>(grid, stream, a, w0);
     default: return launch_strip_kernel<SPLIT, 0, COUNT>(grid, stream, a, w0);
