@@ -479,8 +479,8 @@ __global__ __launch_bounds__(512, 4) void gram_block_kernel(GramArgs a, uint32_t
 //     across the tile row with the strip inner, so that a band's rows are
 //     written end to end, and three work-groups per CU for large outputs (the
 //     fewer bytes being written at a time, the better: 4.16 ms with four; at two
-//     the loads are no longer hidden, 4.34).  N = 100000, d = 40: 3856 us, 4355
-//     in column groups; N = 20000 159 and 182;
+//     the loads are no longer hidden, 4.34; kStripIdle).  N = 100000, d = 40:
+//     3856 us, 4355 in column groups; N = 20000 159 and 182;
 //   - more: column groups of kStripGroup tiles, group outer, strip next, tile
 //     inner: a group's column points then stay in L2 across its 8 strips,
 //     which the wider operands need more (d = 64 split: 5.05 ms, 5.25 in
@@ -508,8 +508,18 @@ constexpr uint32_t kStripBand = 4;
 // (KPC: the padded feature count of an instance; those up to 64 all have one)
 template <bool SPLIT, int KPC>
 constexpr bool kStripBands = KPC != 0 && KPC * (SPLIT ? 2 : 1) <= 64;
-constexpr uint32_t kStripIdleLds = 16 * 1024;               // leaves three work-groups per CU
-constexpr uint64_t kStripSmall = (uint64_t)64 << 20;        // output bytes
+// Three work-groups per CU instead of four, by dynamic LDS that no thread uses:
+// in bands with more than 16 features (parts counted), for outputs from 64 MB
+// on.  Three / four, us: d = 64 BF16 N = 3500 13.3 / 11.7, 4096 14.0 / 14.9,
+// 5300 17.8 / 16.9, 5793 18.8 / 19.7, 8192 29.4 / 30.5, 11585 56.7 / 55.6, 16384
+// 111 / 118, 46000 797 / 862; d = 32 split 5793 19.5 / 20.4, 46000 800 / 849; d =
+// 16 split 8192 28.8 / 27.3, 16384 113 / 120, 46000 889 / 897.  A single step of
+// 16 features loads too little to be hidden by fewer: d = 8 BF16 5793 19.7 /
+// 18.5, 11585 53.1 / 48.0, 16384 107 / 110, 46000 809 / 801, 80000 2459 / 2423.
+template <bool SPLIT, int KPC>
+constexpr bool kStripIdle = kStripBands<SPLIT, KPC> && KPC * (SPLIT ? 2 : 1) > 16;
+constexpr uint32_t kStripIdleLds = 16 * 1024;
+constexpr uint64_t kStripSmall = (uint64_t)64 << 20;  // output bytes
 
 template <bool BANDS>
 __device__ __forceinline__ void strip_order(uint32_t w, uint32_t &I, uint32_t &k, uint32_t &J) {
@@ -666,7 +676,7 @@ __global__ __launch_bounds__(kStripWaves * 64, 8) void gram_strip_kernel(GramArg
 template <bool SPLIT, int KPC, bool COUNT>
 static void launch_strip_kernel(dim3 grid, hipStream_t stream, const GramArgs &a, uint32_t w0) {
   const uint64_t N = (uint64_t)a.N;
-  const uint32_t lds = kStripBands<SPLIT, KPC> && N * (N + 1) * 2 >= kStripSmall ? kStripIdleLds : 0;
+  const uint32_t lds = kStripIdle<SPLIT, KPC> && N * (N + 1) * 2 >= kStripSmall ? kStripIdleLds : 0;
   hipLaunchKernelGGL((gram_strip_kernel<SPLIT, KPC, COUNT>), grid, dim3(kStripWaves * 64), lds, stream, a, w0,
                      grid.x);
 }
