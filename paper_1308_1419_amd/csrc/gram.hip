@@ -361,13 +361,14 @@ __global__ __launch_bounds__(512, 4) void gram_block_kernel(GramArgs a, uint32_t
   load_stage(0);
   if (stages > 1) load_stage(1);
   for (int s = 0; s < stages; ++s) {
-    // this wave's share of stage s has landed (the loads complete in order)
+    // this wave's share of stage s has landed (the loads complete in order) and
+    // its reads of stage s - 1 have returned
     if (s + 1 < stages)
-      __builtin_amdgcn_s_waitcnt(0x0F70 | kBlkLoads);  // vmcnt(kBlkLoads)
+      __builtin_amdgcn_s_waitcnt(0x0070 | kBlkLoads);  // vmcnt(kBlkLoads) lgkmcnt(0)
     else
-      __builtin_amdgcn_s_waitcnt(0x0F70);
-    // ... and every wave's, and stage s - 1 is read (no fence: it would wait
-    // for the loads in flight; the empty asm keeps the LDS reads below)
+      __builtin_amdgcn_s_waitcnt(0x0070);
+    // ... and every wave's (no fence: it would wait for the loads in flight; the
+    // empty asm keeps the LDS reads below)
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     const unsigned char *buf = ops + (s % 3) * kBlkStage;
