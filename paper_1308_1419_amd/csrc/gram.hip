@@ -297,9 +297,15 @@ __device__ __forceinline__ f32x16 gram_step(f32x16 acc, bf16x8 ah, bf16x8 al, bf
 
 // Eight waves as 2 x 4, each on 64 x 64 cells (2 x 2 MFMA blocks).  Stage s
 // holds the fragments of the work-group's 12 point blocks for two k-steps
-// (split: the high and low parts of one), 24 KB, loaded straight into LDS
-// two stages ahead of their use: three buffers, one barrier a stage, two
-// work-groups per CU.
+// (split: the high and low parts of one), 24 KB, loaded straight into LDS:
+// three buffers, one barrier a stage, two work-groups per CU.  The loads are
+// issued two stages ahead, but the compiler, which cannot tell the buffers
+// apart, waits for all of them in front of a stage's first LDS read, so they
+// have one stage of products to land in.  (Three arrays, without that wait: 711
+// against 697 us, N = 30011, d = 200 split.)  Three buffers start with two
+// stages in flight; two, and loads one stage ahead: 755 against 729 us there,
+// 1552 against 1478 at N = 50000, d = 256, but 4836 against 4902 at N = 100000,
+// d = 64 split, where a block has four stages.
 constexpr int kBlkRows = 128;
 constexpr int kBlkFrags = 2 * (kBlkRows / 32 + 8);  // per stage
 constexpr int kBlkStage = kBlkFrags * 1024;

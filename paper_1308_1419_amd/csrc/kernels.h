@@ -98,7 +98,7 @@ struct GramArgs {
   int64_t N;
   int d;
   int64_t ldx;
-  const uint16_t *Xb;  // BF16 points, padded: ceil(N/256)*256 rows of KP features
+  const uint16_t *Xb;  // BF16 points in MFMA fragments: ceil(N/256)*256 points, KP features
   const uint16_t *Xlo; // split mode: BF16 low parts x - hi, same layout; else nullptr
   const float *nrm;    // squared norms of the represented points
   int KP;              // features padded to a multiple of 16
@@ -108,7 +108,7 @@ struct GramArgs {
 
 // BF16 Gram-form EDM (packed), workspace of gram_workspace_bytes(N, d,
 // split); split = the hi + lo representation with three products.  ts
-// selects the kernel: 128 the eight-wave tiles, 256 the 32-row strips.
+// selects the kernel: 128 the 128 x 256 blocks, 256 the 32-row strips.
 size_t gram_workspace_bytes(int64_t N, int d, bool split);
 bool gram_supported(int64_t N, int ts);
 hipError_t launch_gram(const float *X, int64_t N, int d, int64_t ldx, float *D, void *ws, bool split,
