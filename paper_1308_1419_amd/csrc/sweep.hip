@@ -290,11 +290,20 @@ template <int D>
 __global__ __launch_bounds__(kBatchThreads, 8) void edm_batched_sweep_kernel(
     const float *__restrict__ X, const int64_t *__restrict__ point_off,
     const int64_t *__restrict__ oo, int32_t S, float *__restrict__ out) {
-  __shared__ __align__(16) float xs[kBatchLdsFloats];
-  // table of a chunk: first position of each set (relative to the chunk's
-  // first; one more entry ends the last) and its points' place in xs
-  __shared__ int32_t tab_o[kBatchTable + 1];
-  __shared__ int32_t tab_p[kBatchTable];
+  // The table of a chunk comes first, within the reach of an instruction's
+  // 16-bit offset: behind the points each array takes an address register of
+  // its own, and d = 4 spills one (the reload waits for every store).
+  struct Lds {
+    // first position of each set (relative to the chunk's first; one more entry
+    // ends the last) and its points' place in xs
+    int32_t tab_o[kBatchTable + 1];
+    int32_t tab_p[kBatchTable];
+    __align__(16) float xs[kBatchLdsFloats];
+  };
+  __shared__ Lds lds;
+  auto &xs = lds.xs;
+  auto &tab_o = lds.tab_o;
+  auto &tab_p = lds.tab_p;
   const uint64_t first = (uint64_t)oo[0];
   const uint64_t total = (uint64_t)oo[S];
   const uint64_t units = (total - first + kBatchUnit - 1) / kBatchUnit;
