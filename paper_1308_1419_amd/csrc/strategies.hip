@@ -601,12 +601,19 @@ static hipError_t launch_wide_rows(const EdmArgs &a) {
   return hipSuccess;
 }
 
-// Cells from which a work-group takes 4, and (rho 16 and 32) 8 block rows:
-// below, the fewer work-groups leave the chip idle.  Against one block per
-// work-group, us: N = 1400, d = 64, rho 32: 16.5 against 14.5; 2000: 23.6
-// against 25.4; d = 16, rho 16 at 2000: 8.3 against 10.8.  Eight rows against
-// four: N = 3000, d = 24, rho 16: 14.6 against 13.9; N = 5500, d = 16, rho 16
-// and 32: 28.7 and 35.5 against 30.5 and 39.0.
+// Cells (N^2 / 2) from which a work-group takes 4, and (rho 16 and 32) 8 block
+// rows: below, the fewer work-groups leave the chip idle, the more so the longer
+// a block takes (d, rho).  One / 4 rows, us, full layout, around 2^20 cells:
+//   N = 1000   rho 8, d = 5 4.1 / 3.9, d = 64 5.8 / 6.7   rho 16, d = 32 4.3 / 4.8
+//   N = 1200   rho 8, d = 5 4.8 / 3.7, d = 64 7.1 / 7.0   rho 16, d = 32 5.1 / 4.9
+//   N = 1449   rho 8, d = 5 6.1 / 4.5, d = 64 9.0 / 9.0   rho 16, d = 32 6.4 / 6.1
+//              rho 32, d = 5 6.3 / 5.1, d = 64 12.6 / 12.6
+//   N = 2000   rho 8, d = 64 14.6 / 12.3   rho 32, d = 64 19.0 / 17.7
+// 4 / 8 rows around 6 * 2^20:
+//   N = 3000   rho 16, d = 5 9.2 / 8.9, d = 64 22.5 / 23.5   rho 32, d = 64 27.1 / 29.3
+//   N = 3548   rho 16, d = 5 11.3 / 10.6, d = 64 29.2 / 29.0   rho 32, d = 5 14.0 / 13.4,
+//              d = 64 36.2 / 37.3
+//   N = 4500   rho 16, d = 64 43.5 / 42.8   rho 32, d = 64 54.0 / 52.3
 constexpr uint64_t kWideRows4 = 1 << 20;
 constexpr uint64_t kWideRows8 = 6 << 20;
 template <int RHO, int LAYOUT>

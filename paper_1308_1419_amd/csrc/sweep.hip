@@ -186,9 +186,10 @@ __global__ __launch_bounds__(256) void edm_sweep_kernel(const float *__restrict_
 // triangles.  A persistent grid of kBatchWgsPerCu 1024-thread work-groups per
 // CU: work-group b of G owns the units [U b / G, U (b + 1) / G) of kBatchUnit
 // positions, one contiguous stretch of the output, and walks it in chunks
-// whose points it stages in LDS, so that a chunk's stores never wait (vmcnt
-// counts loads and stores alike, and a wait for a load waits for every store
-// issued before it):
+// whose points it stages in LDS.  No wait for a global load then stands between
+// a chunk's stores (vmcnt counts loads and stores alike, and a wait for a load
+// waits for every store issued before it); what they do wait for is
+// kBatchPending.  The chunks:
 //   - a full chunk inside one set: the set's points, staged once when the walk
 //     enters the set, 16 positions per lane in an unrolled loop;
 //   - anything else (the end of a set, sets smaller than a chunk, the end of
@@ -217,9 +218,15 @@ constexpr int kBatchLdsFloats = 16384;                  // 64 KB
 constexpr int kBatchWgsPerCu = 2;
 // Stores a wave leaves unfinished when it goes on to the next (vmcnt): the
 // write rate falls with the bytes that are being written at a time, and 32
-// waves a CU with 16 stores of 256 bytes each would have 128 KB.  1024 sets of
-// 64 to 4096 points, d = 3: 2233, 2203, 2239, 2279 and 2283 us for 1, 2, 3, 4
-// and 8, 2272 with no wait; 500 sets of 250 to 1000 points 98 to 100 in all.
+// waves a CU with 16 stores of 256 bytes each would have 128 KB.  All on the
+// same buffers in one process, us, no wait / 0, 1, 2, 3, 4, 8 stores (spread 1 %):
+//   1024 sets of 64 to 4096 points, d = 1  2258 / 2266 2200 2199 2218 2237 2243
+//                                   d = 2  2252 / 2270 2213 2197 2223 2250 2249
+//                                   d = 3  2281 / 2296 2219 2209 2237 2264 2284
+//                                   d = 4  2300 / 2330 2239 2225 2253 2285 2309
+//   64 sets of 4096 points, d = 3           430 /  426  413  411  415  424  430
+//   300 sets of 3000 points, d = 3         1067 / 1078 1049 1043 1050 1066 1065
+//   500 sets of 250 to 1000 points, d = 3   103 /  105  102  102  103  103  103
 constexpr int kBatchPending = 2;
 
 // A point from LDS.  Four floats start on 16 bytes (points sit on multiples
