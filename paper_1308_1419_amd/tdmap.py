@@ -494,10 +494,26 @@ def stress_backward(X, delta, layout: str = "packed", rho: int = 0,
     return loss, out
 
 
+def _least_cells(points: int, sets: int) -> int:
+    """The fewest packed cells that `points` points in `sets` sets have (sets of
+    equal size, to one point)."""
+    n, more = divmod(points, sets)
+    return (sets - more) * packed_size(n) + more * packed_size(n + 1)
+
+
 def edm_batched(X_cat, point_off, out_off, rho: int = 0, out=None, workspace=None):
     """Packed EDMs of many point sets in one launch (see tdmap_edm_batched).
     ``point_off`` / ``out_off`` are int64 CUDA tensors of length S+1; the
-    total output size is read from ``out_off`` only when ``out`` is None."""
+    total output size is read from ``out_off`` only when ``out`` is None.
+
+    ``rho = 0`` takes the autotuner's decision for S sets of the mean size.
+    With ``out`` given, the rows of ``X_cat`` stand for ``point_off[S]``, and
+    once a decision is there the offsets are not read on the host: pass
+    ``X_cat[:total]`` of a longer buffer, or the decision may be that of larger
+    sets (any decision gives the right cells).  If ``out`` is too small for that
+    many points, if there is no decision yet or with ``out = None`` the library
+    reads ``point_off[S]`` back, waits for the stream and refuses a negative
+    total."""
     torch = _torch()
     X_cat = _points(X_cat)
     d = X_cat.shape[1]
@@ -508,17 +524,19 @@ def edm_batched(X_cat, point_off, out_off, rho: int = 0, out=None, workspace=Non
         raise ValueError("point_off must hold S+1 offsets")
     _device_tensor(point_off, "point_off", torch.int64, X_cat.device)
     _device_tensor(out_off, "out_off", torch.int64, X_cat.device, numel=S + 1)
-    if out is None:
+    waits = out is None
+    if waits:
         total = int(out_off[-1].item())
         out = torch.empty(total, dtype=torch.float32, device=X_cat.device)
     # the size of out against out_off[S] would need a synchronising read of
     # the device offsets: only its type, device and contiguity are checked
     _device_tensor(out, "out", torch.float32, X_cat.device)
-    if rho == 0 and S > 0:
+    rows = X_cat.shape[0]
+    if rho == 0 and S > 0 and not waits and out.numel() >= _least_cells(rows, S):
         # the library reads point_off[S] back to look its decision up by the
         # mean set size (18 us and a wait for the stream); the rows of X_cat
-        # give the same size without it (any decision is a right answer)
-        rho = tdmap_tuned_rho(OP_BATCHED, 0, X_cat.shape[0] // S, d, S)
+        # give it without, unless out shows that there are fewer points
+        rho = tdmap_tuned_rho(OP_BATCHED, 0, rows // S, d, S)
     workspace, ws_ptr, ws_len = _workspace(workspace, X_cat.device, OP_BATCHED, 0, d, S, rho, 0)
     tdmap_edm_batched(X_cat.data_ptr(), d, S, point_off.data_ptr(), out_off.data_ptr(),
                       out.data_ptr(), rho, ws_ptr, ws_len, _stream())
