@@ -227,10 +227,14 @@ def _torch():
 def _stream() -> int:
     """torch's current stream of the current device.  The handle is read
     without building a Stream object, which costs 3 us a call (4 to 16 in
-    autograd's thread) against 0.3."""
+    autograd's thread) against 0.3, where torch has the two functions (they are
+    not part of its interface)."""
     torch = _torch()
     if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            pass
     return torch.cuda.current_stream().cuda_stream
 
 
