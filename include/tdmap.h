@@ -360,17 +360,23 @@ int tdmap_stream_fill(float *buf, uint64_t n, float value, void *stream);
  * Launch statistics of a strategy, in closed form (host only): out[0] =
  * blocks launched, out[1] = fully idle blocks (blocks that write no cell),
  * out[2] = idle threads (threads that write no cell), for the one-cell-per-
- * thread launch with rho x rho blocks.  Sec. II-A: BB leaves n(n-1)/2 blocks
- * idle, LTM none (its idle threads are the upper halves of the n diagonal
- * blocks, about n/2 block equivalents).
+ * thread launch with rho x rho blocks, one per work-group (see
+ * tdmap_count_waste for the launches that differ).  Sec. II-A: BB leaves
+ * n(n-1)/2 blocks idle, LTM none (its idle threads are the upper halves of the
+ * n diagonal blocks, about n/2 block equivalents).
  * Errors: INVALID for a NULL out, N < 0, rho < 1 or an unknown strategy.
  */
 int tdmap_waste_counts(int32_t strategy, int64_t N, int32_t rho, int64_t out[3]);
 
 /*
  * The same statistics counted on the device by an instrumented variant of
- * the strategy's kernel (it evaluates the map and filters exactly as the
- * timed kernel does, and counts instead of storing).
+ * the strategy's one-cell-per-thread kernel, one rho x rho block per
+ * work-group (it evaluates the map and filters exactly as the kernel that
+ * stores for d <= 4 does, and counts instead of storing).  Launches with d > 4
+ * stage their points and place the same blocks, but a large LTM one
+ * (N^2 / 2 >= 2^20) gives each work-group four or eight block rows, idle
+ * work-groups past the last column among them: neither these counts nor the
+ * closed forms describe its work-groups.
  *   counts  device, 3 uint64 (blocks, fully idle blocks, idle threads),
  *           overwritten.
  * rho must be 8, 16 or 32.

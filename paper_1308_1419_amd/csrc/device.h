@@ -63,6 +63,23 @@ __device__ __forceinline__ void g_lambda_uniform(uint32_t lam, uint32_t &i, uint
   j = (uint32_t)c;
 }
 
+// g(lambda) for lambda < 2^28 that differs from lane to lane.
+__device__ __forceinline__ void g_lambda_small(uint32_t lam, uint32_t &i, uint32_t &j) {
+  const float x = __builtin_fmaf(2.0f, (float)lam, 0.25f);
+  const float s = x * __builtin_amdgcn_rsqf(x);
+  int32_t r = (int32_t)__builtin_fmaxf(s - 0.5f, 0.0f);
+  int32_t c = (int32_t)lam - ((r + 1) >> 1) * (r | 1);  // T(r) = ((r + 1) / 2) (r | 1)
+  if (c < 0) {
+    c += r;
+    --r;
+  } else if (c > r) {
+    c -= r + 1;
+    ++r;
+  }
+  i = (uint32_t)r;
+  j = (uint32_t)c;
+}
+
 // q = u / n and the remainder for values that are the same in every lane,
 // u < 2^24 and q + 1 < 2^22: the single-precision quotient is off by at most
 // one, repaired on the scalar unit.

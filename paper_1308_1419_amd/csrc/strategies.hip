@@ -9,9 +9,11 @@
 // blocks of one block column (wide_rows_kernel).
 //
 // Each kernel has two twins that evaluate the same map and filters: one
-// counts blocks / fully idle blocks / idle threads instead of storing, the
-// other is the paper's dummy kernel (Sec. III-A, Sec. IV), which measures
-// the cost of the map alone.
+// counts blocks / fully idle blocks / idle threads instead of storing (one
+// block per work-group, as for up to four features and in wide_cell_kernel;
+// the work-groups of wide_rows_kernel are not counted), the other is the
+// paper's dummy kernel (Sec. III-A, Sec. IV), which measures the cost of the
+// map alone.
 #include <type_traits>
 
 #include "device.h"

@@ -245,23 +245,6 @@ __device__ __forceinline__ void lds_pt(const float *p, float (&v)[D]) {
   }
 }
 
-// g(lambda) for lambda < 2^28 that differs from lane to lane.
-__device__ __forceinline__ void g_lambda_small(uint32_t lam, uint32_t &i, uint32_t &j) {
-  const float x = __builtin_fmaf(2.0f, (float)lam, 0.25f);
-  const float s = x * __builtin_amdgcn_rsqf(x);
-  int32_t r = (int32_t)__builtin_fmaxf(s - 0.5f, 0.0f);
-  int32_t c = (int32_t)lam - ((r + 1) >> 1) * (r | 1);  // T(r) = ((r + 1) / 2) (r | 1)
-  if (c < 0) {
-    c += r;
-    --r;
-  } else if (c > r) {
-    c -= r + 1;
-    ++r;
-  }
-  i = (uint32_t)r;
-  j = (uint32_t)c;
-}
-
 // PER x 1024 positions inside one set, from its position lam on; xp: the
 // set's points in LDS, o: the position's cell.  The walk keeps the LDS
 // offsets iD = i D and jD = j D (additions only; j > i is jD > iD, and a row
