@@ -193,7 +193,9 @@ int tdmap_edm(const float *X, int64_t N, int32_t d, int64_t ldx,
  * g(lambda) (Sec. II-A, Eq. (2)), so the shards are equal to one block and
  * need no exchange; the union of all shards' writes is tdmap_edm's output
  * for the same kernel, bit for bit, and different shards write disjoint
- * cells.  Every shard must cut the same block space, so the kernel is named:
+ * cells.  Every shard must cut the same block space, so the kernel is named
+ * (TDMAP_FULL, rho = 256: D's 16-byte alignment and ldd a multiple of 4, or
+ * not, must be alike on all shards, as these choose the strips' width):
  *   strategy  TDMAP_LTM.
  *   rho       TDMAP_FP32: 64, 128 or 256 (the tiles and strips of tdmap_edm,
  *             d <= 4); the Gram precisions: 128 or 256.

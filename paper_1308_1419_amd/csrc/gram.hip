@@ -23,12 +23,13 @@
 //     order of the FP32 strips), so that the writes in flight stay in a
 //     compact window of the packed output and small N makes more
 //     work-groups.
-// Measured (us, blocks / strips, prologue included): N = 100000, d = 64
-// 4570 / 3920 (BF16), 4740 / 5050 (split); N = 50000, d = 256 1480 / 1940;
-// N = 30011, d = 200 split 700 - 732 / 880; N = 2000, d = 100 16 / 12.2.  The
-// autotuner times both.  With row-major operands, staged through LDS in the
-// strips and loaded by every lane on its own in 128 x 128 tiles, the same
-// sizes took, in the faster of the two, 4400, 6640, 2946, 1860 and 15.3 us.
+// Measured (us, blocks / strips, prologue included, launches back to back on
+// one box, the larger outputs 5 to 10 % more on others): N = 100000, d = 64
+// 4052 / 3665 (BF16), 4300 / 4772 (split); N = 50000, d = 256 1390 / 1886; N =
+// 30011, d = 200 split 739 / 853; N = 2000, d = 100 15.8 / 10.7.  The autotuner
+// times both.  With row-major operands, staged through LDS in the strips and
+// loaded by every lane on its own in 128 x 128 tiles, the same sizes took, in
+// the faster of the two and on the same box, 3973, 6271, 2833, 1858 and 15.0 us.
 //
 // Split mode (precision BF16X3): each point is held as x = hi + lo with
 // hi = bf16(x) and lo = bf16(x - hi) (x - hi is exact in FP32, and hi + lo
