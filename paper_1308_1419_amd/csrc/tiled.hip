@@ -133,8 +133,15 @@ __global__ __launch_bounds__(256) void edm_tile_kernel(EdmArgs a, uint32_t lam0)
 // row I are then numbered u = k (I + 1) + J, strip k outer and tile column J
 // inner, so the work-groups in flight finish a few whole rows of the triangle
 // before they move down instead of spreading over the many rows of whole
-// tiles.  BB: an S n x n grid, blockIdx.y = I, blockIdx.x = k n + J,
-// returning at once for J > I.
+// tiles.  BB: an S n' x n grid, blockIdx.y = I, blockIdx.x = k n' + J,
+// returning at once for J > I.  n' is n made odd: consecutive work-groups go to
+// the eight XCDs in turn, so with an even n a tile column's strips would all go
+// to some of them, and the low columns, which every row has, make those late
+// (n = 8: column J on XCD J alone).  n' = n / n made odd, us: full, N = 8192, d =
+// 1, 3, 4 35.6 / 24.7, 34.5 / 25.6, 38.4 / 25.6; packed, N = 12000 54.7 / 47.3,
+// 54.5 / 47.8, 55.1 / 48.5; full, N = 9217 (n = 10) 43.5 / 45.1, 42.7 / 44.2.
+// Turning the columns by k mod 8 instead breaks up the rows: full, N = 12000
+// 64.7, 65.6, 55.5 against 58.3, 52.4, 50.9.
 //
 // VEC (full layout, D 16-byte aligned, ldd a multiple of 4): a lane owns
 // four consecutive columns and each non-temporal 16-byte store writes a 1 KB
@@ -220,8 +227,9 @@ __global__ __launch_bounds__(256) void edm_band_kernel(const float *__restrict__
   uint32_t I, J, k;
   if constexpr (BB) {
     I = blockIdx.y;
-    k = blockIdx.x / gridDim.y;
-    J = blockIdx.x - k * gridDim.y;
+    const uint32_t cols = gridDim.y | 1;
+    k = blockIdx.x / cols;
+    J = blockIdx.x - k * cols;
     if (J > I) return;
   } else {
     const uint32_t w = w0 + xcd_contiguous(blockIdx.x, gridDim.x);
@@ -303,7 +311,7 @@ static hipError_t launch_band_t(bool bb, const EdmArgs &a) {
   const uint32_t lds = band_bytes(a) >= B::kCached ? B::kIdleLds : 0;
   if (bb) {
     hipLaunchKernelGGL((edm_band_kernel<D, LAYOUT, VEC, SMALL, true, DENSE>),
-                       dim3((uint32_t)(B::S * nb), (uint32_t)nb), dim3(256), lds, a.stream, a.X,
+                       dim3((uint32_t)(B::S * (nb | 1)), (uint32_t)nb), dim3(256), lds, a.stream, a.X,
                        (uint32_t)a.N, a.ldx, a.D, a.ldd, 0u);
     return hipGetLastError();
   }

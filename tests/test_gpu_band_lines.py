@@ -76,3 +76,16 @@ def test_one_feature_costs_no_more_than_two(N):
     X = [torch.from_numpy(synth.uniform_points(N, d, seed=N)).cuda() for d in (1, 2)]
     one, two = _shortest([lambda x=x: tdmap.edm(x, rho=256, out=out, ldd=ld) for x in X])
     assert one <= 1.06 * two
+
+
+def test_bounding_box_strips_fill_all_xcds():
+    # 8192 points in 512-column tiles make 16 a row.  BB's strips, dealt to the
+    # eight XCDs in turn, put a tile column on one XCD then and took 1.53 times
+    # LTM's time; with 17 work-groups per strip 1.09.  At most 1.25.
+    assert torch.cuda.is_available()
+    N = 8192
+    out = torch.empty(N * (N + 1) // 2, dtype=torch.float32, device="cuda")
+    X = torch.from_numpy(synth.uniform_points(N, 3, seed=8)).cuda()
+    ltm, bb = _shortest([lambda s=s: tdmap.edm(X, layout="packed", strategy=s, rho=256, out=out)
+                         for s in ("ltm", "bb")])
+    assert bb <= 1.25 * ltm
