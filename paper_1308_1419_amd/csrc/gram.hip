@@ -215,6 +215,46 @@ __device__ __forceinline__ void recompute_pairs(const GramArgs &a, const uint16_
   }
 }
 
+// Recomputes a wave's close pairs where they are, for up to eight features (a
+// partial sum of exact_dist8 then has one of them): bit m of the mask as in
+// recompute_close, a column of pairs to 16 bits.  A lane keeps its column's
+// point, and the row points are the same in each half of the wave, so a step
+// loads two points for up to 64 pairs where the list's eight lanes a pair load
+// 16 for 8; but every step with a pair in some lane is taken.  Points off the
+// origin (N(3, 1), 87 to 99 % of the pairs close), N = 12000, d = 1, 2, 4, 8: 96
+// 103 125 194 us, 474 488 511 526 from the list, 121 132 303 1073 lane by lane
+// without kept points; N(0, 1), 23, 13, 4 and 0.6 %: 96 103 120 104 and 176 122 81
+// 58.  Hence the line in the caller, by features and the fullest lane's pairs.
+template <bool COUNT, int BITS, typename Pos, typename At>
+__device__ __forceinline__ void recompute_in_place(const GramArgs &a, uint32_t mask, int64_t i0, int64_t j0,
+                                                   Pos pos, At at, uint32_t &nrec) {
+  const int d = a.d;
+  float xj[8];
+#pragma unroll 1
+  for (int m = 0; m < BITS; ++m) {
+    const int p = pos(m);
+    if (m % 16 == 0 && (mask >> m & 0xffffu) != 0) {
+      const float *x = a.X + (j0 + (p & 255)) * a.ldx;
+#pragma unroll
+      for (int k = 0; k < 8; ++k)
+        if (k < d) xj[k] = x[k];
+    }
+    if ((mask >> m & 1u) == 0) continue;
+    const float *x = a.X + (i0 + (p >> 8)) * a.ldx;
+    float s[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      s[k] = 0.0f;
+      if (k < d) {
+        const float t = x[k] - xj[k];
+        s[k] = __builtin_fmaf(t, t, 0.0f);  // (as there: not fused with the sum below)
+      }
+    }
+    if (COUNT) ++nrec;
+    *at(p) = __builtin_amdgcn_sqrtf(((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])));
+  }
+}
+
 // Recomputes a wave's close pairs: bit m of a lane's mask is its pair at
 // position pos(m).  A point with itself, most of the recomputed cells, is
 // exactly 0 and needs no loads; a cell outside the triangle is not stored and
@@ -241,6 +281,11 @@ __device__ __forceinline__ void recompute_close(const GramArgs &a, uint16_t *lis
       if (COUNT) nrec += i0 + (p >> 8) < a.N && i0 + (p >> 8) == j0 + (p & 255);
       *at(p) = 0.0f;
     }
+  }
+  // up to eight features and many pairs (in the fullest lane)
+  if (a.d <= 8 && __builtin_amdgcn_ballot_w64(__builtin_popcount(mask) > (4 + 5 * a.d / 8) * (BITS / 16)) != 0) {
+    recompute_in_place<COUNT, BITS>(a, mask, i0, j0, pos, at, nrec);
+    return;
   }
   int count = 0;  // list entries, the same in every lane
   for (;;) {
