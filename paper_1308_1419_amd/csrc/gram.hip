@@ -215,41 +215,45 @@ __device__ __forceinline__ void recompute_pairs(const GramArgs &a, const uint16_
   }
 }
 
-// Recomputes a wave's close pairs where they are, for up to eight features (a
-// partial sum of exact_dist8 then has one of them): bit m of the mask as in
+// Recomputes a wave's close pairs where they are, for up to F features (feature
+// k belongs to partial sum k mod 8, as in exact_dist8): bit m of the mask as in
 // recompute_close, a column of pairs to 16 bits.  A lane keeps its column's
 // point, and the row points are the same in each half of the wave, so a step
-// loads two points for up to 64 pairs where the list's eight lanes a pair load
-// 16 for 8; but every step with a pair in some lane is taken.  Points off the
-// origin (N(3, 1), 87 to 99 % of the pairs close), N = 12000, d = 1, 2, 4, 8: 96
-// 103 125 194 us, 474 488 511 526 from the list, 121 132 303 1073 lane by lane
-// without kept points; N(0, 1), 23, 13, 4 and 0.6 %: 96 103 120 104 and 176 122 81
-// 58.  Hence the line in the caller, by features and the fullest lane's pairs.
-template <bool COUNT, int BITS, typename Pos, typename At>
+// loads two points' rows for up to 64 pairs where the list's eight lanes a pair
+// load 16 for 8; but every step with a pair in some lane is taken.  In place /
+// from the list / (before the list) lane by lane without a kept point, N =
+// 12000, strips, us: N(3, 1), where 86 to 100 % of the pairs are close, d = 1
+// 96 / 472 / 121, 4 127 / 507 / 303, 9 117 / 585 / 561, 16 248 / 594 / 2125; N(0, 1),
+// 23, 4 and 0.6 %, d = 1 96 / 175 / 121, 4 120 / 81 / 142, 8 104 / 58 / 125.  Hence
+// the line in the caller, by features and the fullest lane's pairs.  With 32
+// features a lane's point costs spills (d = 32, half the pairs close: 737 against
+// 548 from the list).  There the list stays, slower than lane by lane only where
+// nearly every pair is close and the pitch odd (d = 33 2664 against 2409 in the
+// faster kernel; d = 17, N = 513 53 against 42), at even pitches several times
+// as fast (d = 64 1522, 8638).
+template <bool COUNT, int BITS, int F, typename Pos, typename At>
 __device__ __forceinline__ void recompute_in_place(const GramArgs &a, uint32_t mask, int64_t i0, int64_t j0,
                                                    Pos pos, At at, uint32_t &nrec) {
   const int d = a.d;
-  float xj[8];
+  float xj[F];
 #pragma unroll 1
   for (int m = 0; m < BITS; ++m) {
     const int p = pos(m);
     if (m % 16 == 0 && (mask >> m & 0xffffu) != 0) {
       const float *x = a.X + (j0 + (p & 255)) * a.ldx;
 #pragma unroll
-      for (int k = 0; k < 8; ++k)
+      for (int k = 0; k < F; ++k)
         if (k < d) xj[k] = x[k];
     }
     if ((mask >> m & 1u) == 0) continue;
     const float *x = a.X + (i0 + (p >> 8)) * a.ldx;
-    float s[8];
+    float s[8] = {};
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      s[k] = 0.0f;
+    for (int k = 0; k < F; ++k)
       if (k < d) {
         const float t = x[k] - xj[k];
-        s[k] = __builtin_fmaf(t, t, 0.0f);  // (as there: not fused with the sum below)
+        s[k % 8] = __builtin_fmaf(t, t, s[k % 8]);
       }
-    }
     if (COUNT) ++nrec;
     *at(p) = __builtin_amdgcn_sqrtf(((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7])));
   }
@@ -261,7 +265,7 @@ __device__ __forceinline__ void recompute_in_place(const GramArgs &a, uint32_t m
 // set to 0 (both only in blocks that touch the diagonal or the last point,
 // `edge`).  The lanes then hand in one pair each per step, as many steps as
 // the fullest lane has pairs.
-template <bool COUNT, int BITS, typename Pos, typename At>
+template <bool COUNT, int BITS, bool FEW, typename Pos, typename At>
 __device__ __forceinline__ void recompute_close(const GramArgs &a, uint16_t *list, uint32_t mask, bool edge,
                                                 int64_t i0, int64_t j0, Pos pos, At at, uint32_t &nrec) {
   const int l = threadIdx.x & 63;
@@ -282,10 +286,16 @@ __device__ __forceinline__ void recompute_close(const GramArgs &a, uint16_t *lis
       *at(p) = 0.0f;
     }
   }
-  // up to eight features and many pairs (in the fullest lane)
-  if (a.d <= 8 && __builtin_amdgcn_ballot_w64(__builtin_popcount(mask) > (4 + 5 * a.d / 8) * (BITS / 16)) != 0) {
-    recompute_in_place<COUNT, BITS>(a, mask, i0, j0, pos, at, nrec);
-    return;
+  // few features and many pairs (in the fullest lane)
+  if constexpr (FEW) {
+    const int many = a.d < 12 ? 4 + 5 * a.d / 8 : 11;
+    if (a.d <= 16 && __builtin_amdgcn_ballot_w64(__builtin_popcount(mask) > many * (BITS / 16)) != 0) {
+      if (a.d <= 8)
+        recompute_in_place<COUNT, BITS, 8>(a, mask, i0, j0, pos, at, nrec);
+      else
+        recompute_in_place<COUNT, BITS, 16>(a, mask, i0, j0, pos, at, nrec);
+      return;
+    }
   }
   int count = 0;  // list entries, the same in every lane
   for (;;) {
@@ -507,7 +517,7 @@ __global__ __launch_bounds__(512, 4) void gram_block_kernel(GramArgs a, uint32_t
       st[rr * 64 + 32 * (m >> 4) + lr] = __builtin_amdgcn_sqrtf(G);
     }
     if (low != 0)
-      recompute_close<COUNT, 32>(
+      recompute_close<COUNT, 32, true>(
           a, list[q], mask, edge, rw, cw, [&](int m) { return acc_row(m & 15, l) * 256 + 32 * (m >> 4) + lr; },
           [&](int p) { return st + (p >> 8) * 64 + (p & 255); }, nrec);
     __builtin_amdgcn_wave_barrier();  // the wave reads its own LDS writes
@@ -684,7 +694,7 @@ __global__ __launch_bounds__(kStripWaves * 64, 8) void gram_strip_kernel(GramArg
       const float e = acc[v];
       mask |= (uint32_t)gram_close(e, nrow[acc_row(v, l)], ncol) << v;
     }
-    recompute_close<COUNT, 16>(
+    recompute_close<COUNT, 16, KPC == 16>(
         a, list[q], mask, diag || r0 + kStripRows > N, r0, c0 + 32 * q,
         [&](int v) { return acc_row(v, l) * 256 + lr; },
         [&](int p) { return st + (p >> 8) * kStripPitch + 32 * q + (p & 255); }, nrec);

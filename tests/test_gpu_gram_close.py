@@ -1,7 +1,7 @@
 """Gram-form EDM with few features where many pairs are close relative to their
 norms: a wave recomputes them in place instead of from its list.  A feature that
 is 0 in every point adds an exact 0 to the products, the norms and the sums, so
-nine features of which the last are 0, which always take the list, give the same
+33 features of which the last are 0, which always take the list, give the same
 bits."""
 import pytest
 
@@ -20,11 +20,12 @@ def _points(N, d, offset, seed):
 
 @pytest.mark.parametrize("prec", ["bf16_gram", "bf16x3_gram"])
 @pytest.mark.parametrize("offset", [0.0, 0.6, 3.0])
-@pytest.mark.parametrize("N,d", [(2, 1), (33, 8), (300, 1), (300, 2), (300, 3), (600, 5), (257, 7), (1300, 8), (700, 4)])
+@pytest.mark.parametrize("N,d", [(2, 1), (33, 8), (300, 1), (300, 2), (300, 3), (600, 5), (257, 7), (1300, 8), (700, 4),
+                                 (300, 9), (515, 12), (300, 15), (515, 16), (300, 17)])
 def test_in_place_equals_list(N, d, offset, prec):
     assert torch.cuda.is_available()
     X = _points(N, d, offset, seed=N + d)
-    P = torch.zeros((N, 9), device="cuda")
+    P = torch.zeros((N, 33), device="cuda")
     P[:, :d] = X
     W = torch.full((N, d + 3), float("nan"), device="cuda")  # a pitch, 4 bytes past the base
     W[:, 1:d + 1] = X
